@@ -60,7 +60,7 @@ constexpr int kWaves = kThreads / kWave;
 // rotated-space form of P^T (q_r - c)), b = ||r|| (= ||q_r - c|| since P is
 // orthogonal), v_l / v_r = min / max of r / b, Delta = (v_r - v_l) / (2^B_q - 1)
 // and the randomized rounding q_u[i] = min(2^B_q - 1, floor((r_i/b - v_l)/Delta + u_i)),
-// written as s.npl bit planes (and as int8 q_u - s.qoff for the MFMA scan), plus the pair's
+// written as s.npl bit planes (and for the batched scan as int8 q_u - s.qoff, or in the fragment scan's order and format), plus the pair's
 // estimator constants. prep_pair does this for pair g = (query q, list) from
 // the residual rv (this lane's coordinates t * 64 + lane, WS >= W words, a
 // compile-time bound) and the query's norm qn.
@@ -104,6 +104,8 @@ __device__ __forceinline__ void prep_pair(const SearchDev& s, int64_t g, int64_t
   const int npl = NPL > 0 ? NPL : s.npl;   // bit planes (B_q), compile-time when given
   uint64_t* pl = s.planes + g * npl * W;
   int8_t* q8 = s.qu8 ? s.qu8 + g * s.dp : nullptr;
+  const uint32_t q8_at = (uint32_t)(s.frag ? frag_pos(lane) : lane);
+  const float q8_scale = frag_scale(lane);
   // with the MFMA scan, only the pairs whose first chunk is a bootstrap chunk
   // (scanned by the popcount phase 0) need bit planes
   const int64_t r = g - q * s.nprobe;
@@ -124,7 +126,7 @@ __device__ __forceinline__ void prep_pair(const SearchDev& s, int64_t g, int64_t
       const float x = (rv[t] - rmin) * scale;
       const int qu = min(s.qmax, (int)floorf(x + u));
       sq += qu;
-      if (q8) q8[(uint32_t)i] = (int8_t)(qu - s.qoff);
+      if (q8) q8[(uint32_t)(t * kWave) + q8_at] = s.frag ? frag_byte(qu, q8_scale) : (int8_t)(qu - s.qoff);
       if (!planes) continue;
       if constexpr (NPL > 0) {   // all ballots first, then one branch for the stores
         uint64_t w[NPL > 0 ? NPL : 1];
@@ -365,7 +367,9 @@ __device__ __forceinline__ void prep_q_body(const SearchDev& s, int64_t blk) {
       const float x = (rv[t][j] - rmin) * scale;
       qu[j] = min(s.qmax, (int)floorf(x + u));
       sq += qu[j];
-      if (QU8 && act) q8[i] = (int8_t)(qu[j] - s.qoff);
+      if (QU8 && act)
+        q8[s.frag ? t * kWave + frag_pos(l + 16 * j) : i] =
+            s.frag ? frag_byte(qu[j], frag_scale(l)) : (int8_t)(qu[j] - s.qoff);
     }
 #pragma unroll
     for (int jb = 0; jb < 4; ++jb) {
@@ -686,6 +690,9 @@ __global__ __launch_bounds__(kOffThreads) void k_offsets_scan(SearchDev s) {
     }
     __syncthreads();
   }
+  // the batched scan's pair counters, cleared for the grouping
+  if (s.qu8)
+    for (int l = blockIdx.x * kOffThreads + t; l < s.nlist; l += gridDim.x * kOffThreads) s.mf_cnt[l] = 0;
   const int64_t q0 = (int64_t)blockIdx.x * kOffQ + (int64_t)t * 4;
   int64_t v[4][5];
 #pragma unroll
@@ -1410,7 +1417,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_fin_merge_block(SearchDev s, 
 }
 
 // ------------------------------------------------------------------ debug
-__global__ void k_debug_pack(const uint8_t* __restrict__ qu, int dp, int W, int npl, int qoff, float b, float vl,
+__global__ void k_debug_pack(const uint8_t* __restrict__ qu, int dp, int W, int npl, int qoff, int frag, float b, float vl,
                              float delta, float pt, PairRec* rec, uint64_t* planes, int8_t* qu8, float* pair_pt,
                              int32_t list, double rd, double ird) {
   // one wave
@@ -1421,7 +1428,7 @@ __global__ void k_debug_pack(const uint8_t* __restrict__ qu, int dp, int W, int 
     const int i = t * kWave + lane;
     const int v = qu[i];
     sq += v;
-    if (qu8) qu8[i] = (int8_t)(v - qoff);
+    if (qu8) qu8[frag ? t * kWave + frag_pos(lane) : i] = frag ? frag_byte(v, frag_scale(lane)) : (int8_t)(v - qoff);
     for (int j = 0; j < npl; ++j) {
       const uint64_t w = __ballot((v >> j) & 1);
       if (lane == 0) planes[j * W + t] = w;
@@ -1630,11 +1637,11 @@ hipError_t launch_finalize(const SearchDev& s, hipStream_t st) {
   return launch_finalize_split(s, 1, nullptr, nullptr, st);
 }
 
-hipError_t launch_debug_pack(const uint8_t* qu, int dp, int W, int npl, int qoff, float b, float vl, float delta,
+hipError_t launch_debug_pack(const uint8_t* qu, int dp, int W, int npl, int qoff, int frag, float b, float vl, float delta,
                              float pt, PairRec* rec, uint64_t* planes, int8_t* qu8, float* pair_pt, int32_t list,
                              hipStream_t st) {
   const double rd = std::sqrt((double)dp);
-  hipLaunchKernelGGL(k_debug_pack, dim3(1), dim3(kWave), 0, st, qu, dp, W, npl, qoff, b, vl, delta, pt, rec,
+  hipLaunchKernelGGL(k_debug_pack, dim3(1), dim3(kWave), 0, st, qu, dp, W, npl, qoff, frag, b, vl, delta, pt, rec,
                      planes, qu8, pair_pt, list, rd, 1.0 / rd);
   return hipGetLastError();
 }

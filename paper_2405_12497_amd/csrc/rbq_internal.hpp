@@ -57,6 +57,17 @@ struct EstEnt {
   int32_t pos;   // list-order position of the code (its slot is the entry's index)
 };
 
+// A main-phase pair of the batched scan, in its list's run of slots: the
+// estimator's constants (PairTerms), the threshold tau - pt of the bound test,
+// the first chunk the bootstrap did not scan, the pair (its quantised query is
+// row g), and where chunk 0's candidates and count go.
+struct MfRow {
+  float a1, a2, a0, coefh;
+  float pt, thr;
+  int32_t first, g;
+  int64_t seg, count;
+};
+
 struct SeedEnt {
   float dist;
   int32_t id;   // original id (< 2^31), -1 for none
@@ -157,6 +168,16 @@ __device__ __forceinline__ int64_t uniform_i64(int64_t v) {
 }
 __device__ __forceinline__ float uniform_f32(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
+// The query operand of the fragment scan (kernels_frag.hip), one byte per
+// dimension: dimension 64 t + x of a pair (x = 32 g + 4 n + m, m < 4) sits at
+// byte 64 t + frag_pos(x) of its row, as the FP8 (E4M3) value frag_scale(x) q_u
+// (0.5, 0.25, 0.125, 0.125 by m; exact for q_u <= 15).
+__device__ __forceinline__ int frag_pos(int x) { return (x & 32) + 8 * (x & 3) + ((x >> 2) & 7); }
+__device__ __forceinline__ float frag_scale(int x) { return (x & 3) == 0 ? 0.5f : (x & 3) == 1 ? 0.25f : 0.125f; }
+__device__ __forceinline__ int8_t frag_byte(int qu, float scale) {
+  return (int8_t)__builtin_amdgcn_cvt_pk_fp8_f32((float)qu * scale, 0.f, 0, false);
 }
 
 // Compile-time integer carried as a type, for dispatching a runtime count to
@@ -284,6 +305,7 @@ struct SearchDev {
   int qoff;                 // int8 copy of q_u holds q_u - qoff (128 for B_q = 8, else 0)
   int metric;               // 0: squared L2; 1: inner product (cosine runs as IP on unit vectors)
   int mfma_f4;              // batched scan on FP8 x FP4 scaled MFMA instead of int8
+  int frag;                 // batched scan by kernels_frag.hip: qu8 rows in fragment order
   int boot_planes_only;     // 1: bit planes only for the pairs phase 0 scans (the rest go to the MFMA scan)
   int mf_rg;                // batched scan: groups of 16 query rows per work unit (1, 2 or 4)
   const float* fip;         // inner product: per code <o_r - c, c>
@@ -337,10 +359,10 @@ struct SearchDev {
   int32_t* q_cand;          // nq
   // MFMA grouping of main-phase pairs by list
   int32_t* mf_cnt;          // nlist: pairs per list
-  int32_t* mf_fill;         // nlist: scatter cursors
   int64_t* mf_pair_off;     // nlist + 1
-  int64_t* mf_unit_off;     // nlist + 1: (chunk, 16-pair group) units per list
-  int32_t* mf_pairs;        // pair ids bucketed by list
+  int64_t* mf_unit_off;     // nlist + 1: (chunk, 16 mf_rg pairs) units per list
+  int32_t* mf_pairs;        // per pair: its rank among its list's main-phase pairs (-1: none)
+  MfRow* mf_rows;           // the main-phase pairs' records by list
   // outputs
   int64_t* out_ids;
   float* out_d;
@@ -357,15 +379,24 @@ hipError_t launch_plan(const SearchDev& s, hipStream_t st);
 // descriptors, which need launch_plan's results.
 hipError_t launch_prep(const SearchDev& s, bool units, hipStream_t st);
 int scan_popcnt_blocks_per_cu(int W, int npl);
-// Row groups of the batched scan for code length dp: `want` (1, 2 or 4; other
-// values mean 1), lowered until the query tile fits a block's LDS.
-int mfma_row_groups(int dp, bool f4, int want);
-int scan_mfma_blocks_per_cu(int dp, bool f4, int rg, bool narrow);
+// The fragment scan (32 rows per unit) takes codes of W <= 16 words with B_q <=
+// 4 (npl == 4); other searches the block form.
+bool scan_frag_available(int W, int npl);
+int scan_frag_blocks_per_cu(int W);
+hipError_t launch_scan_frag(const SearchDev& s, int grid, hipStream_t st);
+hipError_t launch_debug_frag(const SearchDev& s, const PairRec* rec, const int8_t* qu8, int32_t list, int nchunks,
+                             int32_t* ip, int32_t* pc, float* est, float* dist, float* lb, hipStream_t st);
+// Row groups (of 16 query rows) per unit of the batched scan for code length
+// dp: 2 for the fragment scan, else `want` (1, 2 or 4; other values mean 1),
+// lowered until the query tile fits a block's LDS.
+int mfma_row_groups(int dp, bool f4, int npl, int want);
+int scan_mfma_blocks_per_cu(int dp, bool f4, int rg, int npl);
 // phase 0: bootstrap units, 1: main units with the bound filter, 2: parity
 // export of the main-phase table (s.dbg_*).
 hipError_t launch_scan_popcnt(const SearchDev& s, int phase, int grid, hipStream_t st);
-// The main-phase pairs grouped by list (mf_cnt, mf_pair_off, mf_unit_off,
-// mf_pairs), which launch_scan_mfma's units read; independent of tau.
+// The main-phase pairs grouped by list (mf_pair_off, mf_unit_off, mf_rows),
+// which launch_scan_mfma's units read; needs launch_plan (which clears mf_cnt)
+// and tau.
 hipError_t launch_group_mfma(const SearchDev& s, hipStream_t st);
 hipError_t launch_scan_mfma(const SearchDev& s, int phase, int grid, hipStream_t st);
 hipError_t launch_tau(const SearchDev& s, hipStream_t st);
@@ -377,7 +408,7 @@ hipError_t launch_query_order(const int32_t* nprobe_q, int64_t nq, int nprobe, i
                               hipStream_t st);
 
 // debug: list scan with a given quantised query
-hipError_t launch_debug_pack(const uint8_t* qu, int dp, int W, int npl, int qoff, float b, float vl, float delta,
+hipError_t launch_debug_pack(const uint8_t* qu, int dp, int W, int npl, int qoff, int frag, float b, float vl, float delta,
                              float pt, PairRec* rec, uint64_t* planes, int8_t* qu8, float* pair_pt, int32_t list,
                              hipStream_t st);
 // k-means building blocks (kernels_index.hip): max |x| as float bits

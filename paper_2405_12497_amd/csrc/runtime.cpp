@@ -256,7 +256,7 @@ std::vector<DBuf*> rbq_index::all_buffers() {
           &ws.q_ncode, &ws.offs, &ws.counters, &ws.seg, &ws.seg_count, &ws.p0buf, &ws.tau,
           &ws.chunk_qcode,
           &ws.seedk, &ws.q_order, &ws.order_hist, &ws.lstats, &ws.q_boot, &ws.q_rerank, &ws.q_cand, &ws.pair_pt, &ws.q_m, &ws.qn, &ws.nprobe_q, &ws.q_fb, &ws.feats, &ws.tmp,
-          &ws.mf_cnt, &ws.mf_fill, &ws.mf_pair_off, &ws.mf_unit_off, &ws.mf_pairs, &ws.units0,
+          &ws.mf_cnt, &ws.mf_pair_off, &ws.mf_unit_off, &ws.mf_pairs, &ws.mf_rows, &ws.units0,
           &ws.units1, &ws.fin_part, &ws.fin_pst, &ws.tau_part,
           &mlp.w32, &mlp.wbf, &mlp.wfrag, &mlp.grad, &mlp.m, &mlp.v, &mlp.act};
 }
@@ -661,10 +661,14 @@ rbq_status ensure_workspace(rbq_index* idx, int64_t nq, int nprobe, int k, int c
   if (mfma) {
     HIPCHK(w.qu8.ensure((size_t)np * dp));
     HIPCHK(w.mf_cnt.ensure((size_t)idx->nlist * 4));
-    HIPCHK(w.mf_fill.ensure((size_t)idx->nlist * 4));
     HIPCHK(w.mf_pair_off.ensure((size_t)(idx->nlist + 1) * 8));
     HIPCHK(w.mf_unit_off.ensure((size_t)(idx->nlist + 1) * 8));
     HIPCHK(w.mf_pairs.ensure((size_t)np * 4));
+    // a record per pair with codes to scan (the batched scan's main phase has
+    // no unit table, which would take more: 80 bytes per chunk)
+    const int64_t nonempty = std::lower_bound(idx->sizes_desc.begin(), idx->sizes_desc.end(), (int64_t)0,
+                                              std::greater<int64_t>()) - idx->sizes_desc.begin();
+    HIPCHK(w.mf_rows.ensure((size_t)nq * std::max<int64_t>(1, std::min<int64_t>(nprobe, nonempty)) * sizeof(MfRow)));
   }
   HIPCHK(w.pair_choff.ensure((size_t)nq * (nprobe + 1) * 4));
   HIPCHK(w.pair_codeoff.ensure((size_t)nq * (nprobe + 1) * 4));
@@ -678,7 +682,7 @@ rbq_status ensure_workspace(rbq_index* idx, int64_t nq, int nprobe, int k, int c
   HIPCHK(w.seg_count.ensure((size_t)nq * std::max<int64_t>(1, idx->max_chunks(nprobe, chunk)) * 4));
   HIPCHK(w.chunk_qcode.ensure((size_t)nq * std::max<int64_t>(1, idx->max_chunks(nprobe, chunk)) * 4));
   HIPCHK(w.units0.ensure((size_t)nq * std::max<int64_t>(1, idx->max_chunks(nprobe, chunk)) * sizeof(UnitDesc)));
-  HIPCHK(w.units1.ensure((size_t)nq * std::max<int64_t>(1, idx->max_chunks(nprobe, chunk)) * sizeof(UnitDesc)));
+  if (!mfma) HIPCHK(w.units1.ensure((size_t)nq * std::max<int64_t>(1, idx->max_chunks(nprobe, chunk)) * sizeof(UnitDesc)));
   HIPCHK(w.p0buf.ensure((size_t)nq * (boot_codes(k, chunk) - 1 + chunk) * sizeof(EstEnt)));
   HIPCHK(w.tau.ensure((size_t)nq * 4));
   HIPCHK(w.seedk.ensure((size_t)nq * k * sizeof(SeedEnt)));
@@ -765,10 +769,10 @@ SearchDev make_dev(rbq_index* idx, const float* queries, int64_t nq, int nprobe,
   s.q_rerank = (int32_t*)w.q_rerank.p;
   s.q_cand = (int32_t*)w.q_cand.p;
   s.mf_cnt = (int32_t*)w.mf_cnt.p;
-  s.mf_fill = (int32_t*)w.mf_fill.p;
   s.mf_pair_off = (int64_t*)w.mf_pair_off.p;
   s.mf_unit_off = (int64_t*)w.mf_unit_off.p;
   s.mf_pairs = (int32_t*)w.mf_pairs.p;
+  s.mf_rows = (MfRow*)w.mf_rows.p;
   s.units0 = (UnitDesc*)w.units0.p;
   s.units1 = (UnitDesc*)w.units1.p;
   s.chunk_qcode = (int32_t*)w.chunk_qcode.p;
@@ -896,7 +900,8 @@ rbq_status run_search(rbq_index* idx, const float* queries, int64_t nq, const rb
   SearchDev s = make_dev(idx, queries, nq, o.nprobe, o.k, chunk, nprobe_q, o.qid_base, mfma,
                          out_ids, out_d);
   s.mfma_f4 = scan_kernel == RBQ_SCAN_MFMA_FP4 ? 1 : 0;
-  s.mf_rg = mfma_row_groups(idx->dp, s.mfma_f4 != 0, mf_rg);
+  s.mf_rg = mfma_row_groups(idx->dp, s.mfma_f4 != 0, s.npl, mf_rg);
+  s.frag = mfma && scan_frag_available(s.W, s.npl) ? 1 : 0;
   s.boot_planes_only = mfma ? 1 : 0;
   HIPCHK(rec(1));
   HIPCHK(launch_plan(s, st));
@@ -930,7 +935,7 @@ rbq_status run_search(rbq_index* idx, const float* queries, int64_t nq, const rb
   if (mfma) HIPCHK(launch_group_mfma(s, st));
   HIPCHK(rec(4));
   if (mfma) {
-    HIPCHK(launch_scan_mfma(s, 1, scan_grid(idx, nq, chunks, scan_mfma_blocks_per_cu(idx->dp, s.mfma_f4 != 0, s.mf_rg, s.npl == 4)),
+    HIPCHK(launch_scan_mfma(s, 1, scan_grid(idx, nq, chunks, scan_mfma_blocks_per_cu(idx->dp, s.mfma_f4 != 0, s.mf_rg, s.npl)),
                             st));
   } else {
     HIPCHK(launch_scan_popcnt(s, 1, grid, st));
@@ -1636,7 +1641,8 @@ extern "C" rbq_status rbq_debug_scan(rbq_index* idx, int32_t list, const uint8_t
   if (rs != RBQ_OK) return rs;
   Workspace& w = idx->ws;
   SearchDev s = make_dev(idx, nullptr, 1, 1, 1, kDefaultChunk, nullptr, 0, true, nullptr, nullptr);
-  HIPCHK(launch_debug_pack(qu, idx->dp, idx->W, s.npl, s.qoff, scal[0], scal[1], scal[2], scal[3],
+  s.frag = kernel != RBQ_SCAN_POPCNT && scan_frag_available(s.W, s.npl) ? 1 : 0;
+  HIPCHK(launch_debug_pack(qu, idx->dp, idx->W, s.npl, s.qoff, s.frag, scal[0], scal[1], scal[2], scal[3],
                            (PairRec*)w.pairs.p, (uint64_t*)w.planes.p, (int8_t*)w.qu8.p, (float*)w.pair_pt.p,
                            list, st));
   if (kernel == RBQ_SCAN_POPCNT) {
@@ -1668,7 +1674,7 @@ extern "C" rbq_status rbq_debug_scan(rbq_index* idx, int32_t list, const uint8_t
     HIPCHK(hipStreamSynchronize(st));   // the host tables above are stack memory
   }
   s.mfma_f4 = kernel == RBQ_SCAN_MFMA_FP4 ? 1 : 0;
-  s.mf_rg = mfma_row_groups(idx->dp, s.mfma_f4 != 0, 0);
+  s.mf_rg = mfma_row_groups(idx->dp, s.mfma_f4 != 0, s.npl, 0);
   HIPCHK(launch_debug_scan(s, (const PairRec*)w.pairs.p, (const uint64_t*)w.planes.p,
                            (const int8_t*)w.qu8.p, list, kernel, ip, pc, est, dist, lb, st));
   return RBQ_OK;
@@ -1801,7 +1807,9 @@ extern "C" rbq_status rbq_autotune(rbq_index* idx, const float* queries, int64_t
   const int chunks[] = {256, 512, 1024, 2048};
   std::vector<int> kernels = {RBQ_SCAN_POPCNT};
   if (rbq::mfma_available()) kernels.push_back(RBQ_SCAN_MFMA);
-  if (rbq::mfma_available() && idx->prm.bq <= 4) kernels.push_back(RBQ_SCAN_MFMA_FP4);
+  // where the fragment scan serves both, one of them is enough
+  const int npl = idx->prm.bq <= 4 ? 4 : 8;
+  if (rbq::mfma_available() && idx->prm.bq <= 4 && !scan_frag_available(idx->W, npl)) kernels.push_back(RBQ_SCAN_MFMA_FP4);
   for (int64_t m : sizes) {
     TuneEntry best;
     float best_ms = 1e30f;
@@ -1825,9 +1833,9 @@ extern "C" rbq_status rbq_autotune(rbq_index* idx, const float* queries, int64_t
     // expanded code fragment; fewer rows per unit leave more blocks per CU)
     if (best.kernel == RBQ_SCAN_MFMA || best.kernel == RBQ_SCAN_MFMA_FP4) {
       const bool f4 = best.kernel == RBQ_SCAN_MFMA_FP4;
-      const int rg0 = mfma_row_groups(idx->dp, f4, 0);
+      const int rg0 = mfma_row_groups(idx->dp, f4, npl, 0);
       for (int rg : {1, 2, 4}) {
-        if (mfma_row_groups(idx->dp, f4, rg) != rg || rg == rg0) continue;
+        if (mfma_row_groups(idx->dp, f4, npl, rg) != rg || rg == rg0) continue;
         TuneEntry t = best;
         t.mf_rg = rg;
         float ms = 0.f;
