@@ -23,35 +23,13 @@
 #include <algorithm>
 
 #include "rbq_internal.hpp"
+#include "rbq_prep.hpp"
 #include "scan_code.hpp"
 #include "wave_select.hpp"
 #include "rbq_runtime.hpp"
 
 namespace rbq {
 namespace {
-
-// <x_bar, q_bar> = k1 <x_b, q_u> + k2 popcount(x_b) + k0 with k1 = 2 Delta / sqrt(D),
-// k2 = 2 v_l / sqrt(D) and k0 = -(Delta / sqrt(D)) sum(q_u) - sqrt(D) v_l
-// (Sec. 3.3.1-3.3.2), in FP64; rd = sqrt(D) and ird = 1 / rd come from the host.
-__device__ __forceinline__ void pair_coeffs(double vl, double delta, int sq, double rd, double ird,
-                                            PairRec& r) {
-  const double dr = delta * ird;
-  r.k1 = (float)(2.0 * dr);
-  r.k2 = (float)(2.0 * vl * ird);
-  r.k0 = (float)(-dr * (double)sq - rd * vl);
-}
-
-// v_l = rmin / b and Delta = range / ((2^B_q - 1) b) of a pair, in FP64 (0 when b = 0).
-__device__ __forceinline__ void pair_scalars(float rmin, float range, float b, int qmax, double& vl,
-                                             double& delta) {
-  vl = 0.0;
-  delta = 0.0;
-  if (b > 0.f) {
-    const double ib = 1.0 / (double)b;
-    vl = (double)rmin * ib;
-    delta = (double)range * ib / (double)qmax;
-  }
-}
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
@@ -69,7 +47,6 @@ __device__ __forceinline__ void prep_pair(const SearchDev& s, int64_t g, int64_t
                                           float qn) {
   const int lane = lane_id();
   const int W = s.W;
-  PairRec rec;
   float rmin = rv[0], rmax = rv[0], ss = 0.f;
 #pragma unroll
   for (int t = 0; t < WS; ++t) {
@@ -80,20 +57,7 @@ __device__ __forceinline__ void prep_pair(const SearchDev& s, int64_t g, int64_t
     }
   }
   float b = uniform_f32(sqrtf(wave_sum(ss)));
-  // Near a centroid the rotated residual is dominated by the rotation's
-  // rounding (~1e-6 (||q|| + ||c||)): take b from the raw vectors there, so
-  // that b is exactly 0 when the query coincides with the centroid.
-  const float scale_qc = uniform_f32(qn + sqrtf(s.cnorm[list]));
-  if (b <= 1e-4f * scale_qc) {
-    const float* qr = s.q + q * s.dim;
-    const float* c = s.cent + (int64_t)list * s.dim;
-    float acc = 0.f;
-    for (int i = lane; i < s.dim; i += kWave) {
-      const float d = qr[i] - c[i];
-      acc = fmaf(d, d, acc);
-    }
-    b = uniform_f32(sqrtf(wave_sum(acc)));
-  }
+  b = pair_norm(s, q, list, b, qn);
   rmin = wave_min(rmin);
   rmax = wave_max(rmax);
   const float range = rmax - rmin;
@@ -145,25 +109,8 @@ __device__ __forceinline__ void prep_pair(const SearchDev& s, int64_t g, int64_t
     }
   }
   sq = wave_sum_i(sq);
-  if (s.metric != 0) {   // inner product: the pair's constant M_q - <q_r, c> from the raw vectors
-    const float* qr = s.q + q * s.dim;
-    const float* c = s.cent + (int64_t)list * s.dim;
-    float acc = 0.f;
-    for (int i = lane; i < s.dim; i += kWave) acc = fmaf(qr[i], c[i], acc);
-    const float gdot = wave_sum(acc);
-    if (lane == 0) s.pair_pt[g] = s.q_m[q] - gdot;
-  }
-  if (lane == 0) {
-    double vl, delta;
-    pair_scalars(rmin, range, b, s.qmax, vl, delta);
-    pair_coeffs(vl, delta, sq, s.rd, s.ird, rec);
-    rec.b = b;
-    rec.vl = (float)vl;
-    rec.delta = (float)delta;
-    rec.sq = sq;
-    rec.list = list;
-    s.pairs[g] = rec;
-  }
+  if (s.metric != 0) pair_ip_term(s, g, q, list);
+  if (lane == 0) s.pairs[g] = pair_record(s, rmin, range, b, sq, list);
 }
 
 // One wave per PPW consecutive pairs, residuals held in registers (each
@@ -204,13 +151,7 @@ __global__ __launch_bounds__(kThreads) void k_prep_reg(SearchDev s) {
     any = any || act[j];
   }
   if (!any) {   // probe slots past the query's nprobe: empty records, no coordinate reads
-    if (lane < PPW && g0 + lane < npairs) {
-      PairRec rec;
-      rec.k1 = rec.k2 = rec.k0 = rec.b = rec.vl = rec.delta = 0.f;
-      rec.sq = 0;
-      rec.list = -1;
-      s.pairs[g0 + lane] = rec;
-    }
+    if (lane < PPW && g0 + lane < npairs) s.pairs[g0 + lane] = empty_record();
     return;
   }
 #pragma unroll
@@ -246,13 +187,7 @@ __global__ __launch_bounds__(kThreads) void k_prep_reg(SearchDev s) {
     const int64_t g = g0 + j;
     if (g >= npairs) break;
     if (!act[j]) {
-      PairRec rec;
-      if (lane == 0) {
-        rec.k1 = rec.k2 = rec.k0 = rec.b = rec.vl = rec.delta = 0.f;
-        rec.sq = 0;
-        rec.list = -1;
-        s.pairs[g] = rec;
-      }
+      if (lane == 0) s.pairs[g] = empty_record();
       continue;
     }
     prep_pair<WS, NPL>(s, g, g / s.nprobe, list[j], rv[j], sqrtf(wave_sum(qq[j])));
@@ -389,24 +324,7 @@ __device__ __forceinline__ void prep_q_body(const SearchDev& s, int64_t blk) {
     if (act && l == 0) s.pair_pt[g] = s.q_m[q] - acc;
   }
   if (act && l < 4 * W) s.planes[g * 4 * W + l] = myword;
-  if (valid && l == 0) {
-    PairRec rec;
-    if (!act) {
-      rec.k1 = rec.k2 = rec.k0 = rec.b = rec.vl = rec.delta = 0.f;
-      rec.sq = 0;
-      rec.list = -1;
-    } else {
-      double vl, delta;
-      pair_scalars(rmin, range, b, s.qmax, vl, delta);
-      pair_coeffs(vl, delta, sq, s.rd, s.ird, rec);
-      rec.b = b;
-      rec.vl = (float)vl;
-      rec.delta = (float)delta;
-      rec.sq = sq;
-      rec.list = list;
-    }
-    s.pairs[g] = rec;
-  }
+  if (valid && l == 0) s.pairs[g] = act ? pair_record(s, rmin, range, b, sq, list) : empty_record();
 }
 
 template <int W, bool QU8>
@@ -1482,8 +1400,11 @@ hipError_t launch_prep(const SearchDev& s, bool units, hipStream_t st) {
     if (units) hipLaunchKernelGGL(k_units, dim3((unsigned)ublocks), dim3(kThreads), 0, st, s);
     return hipGetLastError();
   }
-  // wide rows: one pair per wave (two up to W = 8), the register bound WS exact
-  // for D = 768 and 960, and B_q = 4 planes compile-time
+  if (launch_prep_wide(s, st)) {
+    if (units) hipLaunchKernelGGL(k_units, dim3((unsigned)ublocks), dim3(kThreads), 0, st, s);
+    return hipGetLastError();
+  }
+  // the rest (B_q > 4 or more than 16 words): one pair per wave, two up to W = 8
   const bool p4 = s.npl == 4;
 #define RBQ_PREP(WS_, PPW_)                                                                          \
   do {                                                                                              \
@@ -1497,8 +1418,6 @@ hipError_t launch_prep(const SearchDev& s, bool units, hipStream_t st) {
     case 2: launch_prep_q<2>(s, ublocks, qblocks, st); return hipGetLastError();
     case 3: launch_prep_q<3>(s, ublocks, qblocks, st); return hipGetLastError();
     case 4: launch_prep_q<4>(s, ublocks, qblocks, st); return hipGetLastError();
-    case 12: RBQ_PREP(12, 1); break;
-    case 15: RBQ_PREP(15, 1); break;
     default:
       if (s.W <= 8) {
         RBQ_PREP(8, 2);

@@ -378,6 +378,9 @@ hipError_t launch_plan(const SearchDev& s, hipStream_t st);
 // Per-pair quantisation (S3); with units = true also the scan's unit
 // descriptors, which need launch_plan's results.
 hipError_t launch_prep(const SearchDev& s, bool units, hipStream_t st);
+// launch_prep's quantisation for codes of 5 to 16 words and B_q <= 4
+// (kernels_prep.hip); false where it does not apply.
+bool launch_prep_wide(const SearchDev& s, hipStream_t st);
 int scan_popcnt_blocks_per_cu(int W, int npl);
 // The fragment scan (32 rows per unit) takes codes of W <= 16 words with B_q <=
 // 4 (npl == 4); other searches the block form.
