@@ -80,7 +80,7 @@ struct WaveLds {
 };
 
 // What a lane holds of its query (column): the estimator's constants, the
-// threshold tau - pt (NaN where the column is not scanned: no bound passes),
+// threshold tau - pt (-inf where the column is not scanned: no bound passes),
 // and where its candidates go.
 struct Column {
   float a1, a2, a0, coefh, pt, thr;
@@ -108,7 +108,7 @@ __device__ int frag_unit(const SearchDev& s, int64_t start, int n, const Column&
   float2 sf;
   float fi = 0.f;
   // this lane's half of every word of its code (past the end: the last code,
-  // whose outputs the NaN code term drops), its factors and inner-product term
+  // whose outputs are dropped), its factors and inner-product term
   auto load = [&](int rb) {
     const uint32_t r = (uint32_t)min(rb + col, n - 1);
     const uint32_t x = (uint32_t)o0 + r;
@@ -140,18 +140,30 @@ __device__ int frag_unit(const SearchDev& s, int64_t start, int n, const Column&
     const int pc = (int)(sw[0] + sw[1]);
     if (grp == 0) {
       const float ct = fbase != nullptr ? -fi : code_term_l2(sf);
-      L.fac[col] = make_float4(sf.x, sf.y, (float)pc, rb + col < n ? ct : __builtin_nanf(""));
+      L.fac[col] = make_float4(sf.x, sf.y, (float)pc, ct);
     }
     wave_lds_sync();
     if (rb + 32 < n) load(rb + 32);   // in flight during this block's products and outputs
     result_wait(acc);
     // bounds without the pair term (as est_y / est_dl on the integer product);
-    // mask: bit 15 - i for a passing output i
-    uint32_t mask = 0;
+    // fails: bit 15 - i is the sign of thr - bound of output i (two cheap
+    // instructions without a lane mask between them). A NaN bound may count as
+    // passing: the rerank drops it.
+    // The factors are read four outputs ahead: left alone, the compiler reads
+    // each right before its use to save registers and waits 16 times.
     float low[16];
+    uint32_t fails = 0;
+    float4 fc[2][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fc[0][i] = L.fac[4 * grp + i];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const float4 f = L.fac[8 * (i >> 2) + 4 * grp + (i & 3)];
+      if ((i & 3) == 0 && i < 12) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) fc[(i >> 2) + 1 & 1][e] = L.fac[8 * (i >> 2) + 8 + 4 * grp + e];
+        asm volatile("" ::: "memory");
+      }
+      const float4 f = fc[(i >> 2) & 1][i & 3];
       const float y = fmaf(c.a1, acc[i], fmaf(c.a2, f.z, c.a0));
       const float d0 = fmaf(f.x, y, f.w);
       low[i] = fmaf(c.coefh, f.y, d0);
@@ -166,25 +178,23 @@ __device__ int frag_unit(const SearchDev& s, int64_t start, int n, const Column&
           dbg_lb[o] = low[i] + c.pt;
         }
       } else {
-        // mask = 2 mask + (low <= thr): the compare's lane mask is the carry
-        asm("v_cmp_le_f32_e32 vcc, %1, %2\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
-            : "+v"(mask)
-            : "v"(low[i]), "v"(c.thr)
-            : "vcc");
+        fails = __builtin_amdgcn_alignbit(fails, __float_as_uint(c.thr - low[i]), 31);
       }
     }
     if constexpr (!DEBUG) {
+      const uint32_t mask = ~fails & 0xFFFFu;
       if (__ballot(mask != 0u) != 0ull) {
         // the column's 32 codes in order, first code at bit 31: this lane's
         // groups of four between its partner's
         uint32_t sp = (mask | (mask << 8)) & 0x00FF00FFu;
         sp = (sp | (sp << 4)) & 0x0F0F0F0Fu;
         const auto pr = __builtin_amdgcn_permlane32_swap(sp, sp, false, false);
-        const uint32_t all = ((uint32_t)pr[0] << 4) | (uint32_t)pr[1];
+        const int left = n - rb;   // codes of the block that exist
+        const uint32_t all = (((uint32_t)pr[0] << 4) | (uint32_t)pr[1]) & (left < 32 ? ~(0xFFFFFFFFu >> left) : ~0u);
+        // each lane's passing outputs one after the other (a few per lane)
 #pragma unroll
         for (int j = 0; j < 4; ++j) L.low[j][lane] = make_float4(low[4 * j], low[4 * j + 1], low[4 * j + 2], low[4 * j + 3]);
         wave_lds_sync();
-        // each lane's passing outputs one after the other (a few per lane)
         uint32_t m = mask << 16;
         while (__ballot(m != 0u) != 0ull) {
           if (m != 0u) {
@@ -194,7 +204,7 @@ __device__ int frag_unit(const SearchDev& s, int64_t start, int n, const Column&
             Cand cd;
             cd.pos = (int32_t)start + rb + code;
             cd.lb = reinterpret_cast<const float*>(&L.low[i >> 2][lane])[i & 3] + c.pt;
-            c.seg[count + __popc(all & ~(0xFFFFFFFFu >> code))] = cd;
+            if (code < left) c.seg[count + __popc(all & ~(0xFFFFFFFFu >> code))] = cd;
           }
         }
         count += __popc(all);
@@ -237,7 +247,7 @@ __device__ __forceinline__ void load_fragments(const int8_t* row, int grp, u32x6
 // turn), so the groups of one chunk run on one XCD and share its L2, then
 // moves on to the other slices. Each wave claims its units by itself.
 template <int WS>
-__global__ __launch_bounds__(kThreads, WS <= 12 ? 3 : 2) void k_scan_frag(SearchDev s) {
+__global__ __launch_bounds__(kThreads, WS <= 6 ? 4 : WS <= 12 ? 3 : 2) void k_scan_frag(SearchDev s) {
   __shared__ WaveLds lds[kWaves];
   WaveLds& L = lds[threadIdx.x / kWave];
   const int lane = lane_id(), col = lane & 31, grp = lane >> 5;
@@ -245,14 +255,31 @@ __global__ __launch_bounds__(kThreads, WS <= 12 ? 3 : 2) void k_scan_frag(Search
   const int x0 = (int)(blockIdx.x % kScanSlices);
   for (int j = 0; j < kScanSlices; ++j) {
     const int x = (x0 + j) % kScanSlices;
-    const int64_t hi = total * (x + 1) / kScanSlices;
     const int64_t lo = total * x / kScanSlices;
+    const int64_t size = total * (x + 1) / kScanSlices - lo;
+    // The slice's first units belong to the waves that start on it, one each; the
+    // rest are claimed from its counter. A counter is only added to where it can
+    // have units left (4096 waves that each tried all eight took 100 us on their
+    // addresses).
+    const int64_t own = (int64_t)kWaves * ((gridDim.x + kScanSlices - 1 - x) / kScanSlices);
     unsigned long long* ctr = s.counters + kScanSliceCtr + kScanSliceStride * x;
+    int64_t next = -1;
+    if (j == 0) {
+      next = (int64_t)kWaves * (blockIdx.x / kScanSlices) + threadIdx.x / kWave;
+    } else {
+      const unsigned long long seen = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (own + uniform_i64((int64_t)seen) >= size) continue;
+    }
     for (;;) {
-      unsigned long long cl = 0;
-      if (lane == 0) cl = atomicAdd(ctr, 1ull);
-      const int64_t u = lo + uniform_i64((int64_t)cl);   // lane 0's claim (every lane is active)
-      if (u >= hi) break;
+      if (next < 0) {
+        if (own >= size) break;
+        unsigned long long cl = 0;
+        if (lane == 0) cl = atomicAdd(ctr, 1ull);
+        next = own + uniform_i64((int64_t)cl);   // lane 0's claim (every lane is active)
+      }
+      if (next >= size) break;
+      const int64_t u = lo + uniform_i64(next);
+      next = -1;
       const int list = wave_find_list(s.mf_unit_off, s.nlist, u);
       const int local = (int)uniform_i64(u - s.mf_unit_off[list]);
       const int64_t p0 = uniform_i64(s.mf_pair_off[list]);
@@ -274,7 +301,7 @@ __global__ __launch_bounds__(kThreads, WS <= 12 ? 3 : 2) void k_scan_frag(Search
       c.a0 = row.a0;
       c.coefh = row.coefh;
       c.pt = row.pt;
-      c.thr = live ? row.thr : __builtin_nanf("");
+      c.thr = live && row.thr == row.thr ? row.thr : -__builtin_inff();
       c.seg = s.seg + row.seg + (int64_t)ch * s.chunk;
       const int count = frag_unit<false, WS>(s, start, n, c, fq, L, nullptr, nullptr, nullptr, nullptr, nullptr,
                                              nullptr, 0);
@@ -303,7 +330,7 @@ __global__ __launch_bounds__(kWave) void k_debug_frag(SearchDev s, const PairRec
   c.a0 = t.a0;
   c.coefh = t.coefh;
   c.pt = t.pt;
-  c.thr = __builtin_nanf("");
+  c.thr = -__builtin_inff();
   c.seg = nullptr;
   (void)frag_unit<true, WS>(s, start, (int)(end - start), c, fq, L, recp, ip, pc, est, dist, lb, lbeg);
 }

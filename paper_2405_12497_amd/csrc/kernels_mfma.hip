@@ -285,8 +285,81 @@ __device__ __forceinline__ int64_t ub64(const int64_t* a, int64_t n, int64_t v) 
 // rank theirs with LDS counters (nlist <= 24,576 of them fit), then each block
 // takes its share of every list with one device atomic per list it met. One
 // atomic per pair on the lists' counters instead, and another per pair to
-// scatter, took 220 us for 1.28 M pairs on 4096 lists; this takes 40 us.
+// scatter, took 220 us for 1.28 M pairs on 4096 lists; counting and ranking
+// take 13 us, the offsets 8 us, the records 48 us. Up to 16,384 pairs are one
+// block, which also computes the offsets.
 constexpr int kGrpThreads = 1024, kGrpPer = 16;
+
+// Exclusive scans of the lists' pair counts and unit counts by one block of
+// kGrpThreads threads (tiles of kOffPer consecutive lists per thread; wave
+// scans, then the 16 wave totals), and the work counters reset. count(l): the
+// pairs of list l.
+constexpr int kOffPer = 4;
+
+template <class Count>
+__device__ __forceinline__ void group_offsets(const SearchDev& s, Count count) {
+  __shared__ int32_t wp[kGrpThreads / kWave], wu[kGrpThreads / kWave];
+  const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
+  if (t == 0) s.counters[2] = 0;
+  if (t < kScanSlices) s.counters[kScanSliceCtr + kScanSliceStride * t] = 0;
+  const int rows = 16 * s.mf_rg;
+  int64_t carry_p = 0, carry_u = 0;
+  for (int base = 0; base < s.nlist; base += kGrpThreads * kOffPer) {
+    const int l0 = base + t * kOffPer;
+    int c[kOffPer], u[kOffPer], lo[kOffPer + 1];
+#pragma unroll
+    for (int i = 0; i <= kOffPer; ++i) lo[i] = s.list_off[min(l0 + i, s.nlist)];
+#pragma unroll
+    for (int i = 0; i < kOffPer; ++i) c[i] = count(min(l0 + i, s.nlist - 1));
+    // a tile's sums fit 32 bits: at most 2^31 pairs in all, and units of at
+    // least one pair and one code each
+    int sp = 0, su = 0;
+#pragma unroll
+    for (int i = 0; i < kOffPer; ++i) {
+      c[i] = l0 + i < s.nlist ? c[i] : 0;
+      u[i] = c[i] > 0 ? ((lo[i + 1] - lo[i] + s.chunk - 1) / s.chunk) * ((c[i] + rows - 1) / rows) : 0;
+      sp += c[i];
+      su += u[i];
+    }
+    int ip = sp, iu = su;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int yp = __shfl_up(ip, o, kWave), yu = __shfl_up(iu, o, kWave);
+      ip += lane >= o ? yp : 0;
+      iu += lane >= o ? yu : 0;
+    }
+    if (lane == kWave - 1) {
+      wp[wave] = ip;
+      wu[wave] = iu;
+    }
+    __syncthreads();
+    int64_t bp = carry_p + ip - sp, bu = carry_u + iu - su;
+    for (int w = 0; w < kGrpThreads / kWave; ++w) {
+      bp += w < wave ? wp[w] : 0;
+      bu += w < wave ? wu[w] : 0;
+      carry_p += wp[w];
+      carry_u += wu[w];
+    }
+#pragma unroll
+    for (int i = 0; i < kOffPer; ++i) {
+      if (l0 + i < s.nlist) {
+        s.mf_pair_off[l0 + i] = bp;
+        s.mf_unit_off[l0 + i] = bu;
+      }
+      bp += c[i];
+      bu += u[i];
+    }
+    __syncthreads();   // the next tile's totals overwrite these
+  }
+  if (t == 0) {
+    s.mf_pair_off[s.nlist] = carry_p;
+    s.mf_unit_off[s.nlist] = carry_u;
+  }
+}
+
+__global__ __launch_bounds__(kGrpThreads) void k_group_offsets(SearchDev s) {
+  group_offsets(s, [&](int l) { return s.mf_cnt[l]; });
+}
 
 __global__ __launch_bounds__(kGrpThreads) void k_group_count(SearchDev s) {
   extern __shared__ int32_t hist[];
@@ -294,30 +367,44 @@ __global__ __launch_bounds__(kGrpThreads) void k_group_count(SearchDev s) {
   const int64_t g0 = (int64_t)blockIdx.x * (kGrpThreads * kGrpPer) + threadIdx.x;
   for (int l = threadIdx.x; l < s.nlist; l += kGrpThreads) hist[l] = 0;
   int list[kGrpPer], rank[kGrpPer];
-  {
-    // clamped reads, all in flight together, then the tests
-    int c0[kGrpPer], c1[kGrpPer], p0[kGrpPer];
+  // four pairs per thread at a time: clamped reads, all in flight together,
+  // then the tests
+  const int64_t left = np - (int64_t)blockIdx.x * (kGrpThreads * kGrpPer);   // pairs from this block on
 #pragma unroll
-    for (int i = 0; i < kGrpPer; ++i) {
-      const int64_t g = g0 + (int64_t)i * kGrpThreads;
-      const int64_t gc = min(g, np - 1);
+  for (int i0 = 0; i0 < kGrpPer; i0 += 4) {
+#pragma unroll
+    for (int i = i0; i < i0 + 4; ++i) list[i] = -1;
+    if ((int64_t)i0 * kGrpThreads >= left) continue;   // uniform
+    int c0[4], c1[4], p0[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int64_t gc = min(g0 + (int64_t)(i0 + e) * kGrpThreads, np - 1);
       const int64_t q = gc / s.nprobe;
       const int64_t o = gc + q;   // choff row stride is nprobe + 1
-      c0[i] = s.pair_choff[o];
-      c1[i] = s.pair_choff[o + 1];
-      p0[i] = s.q_p0[q];
-      list[i] = s.probe[gc];
+      c0[e] = s.pair_choff[o];
+      c1[e] = s.pair_choff[o + 1];
+      p0[e] = s.q_p0[q];
+      l[e] = s.probe[gc];
     }
     // a main-phase chunk remains: chunks before q_p0 were scanned by phase 0
     // (a rank past the query's nprobe has no chunk)
 #pragma unroll
-    for (int i = 0; i < kGrpPer; ++i)
-      list[i] = (g0 + (int64_t)i * kGrpThreads < np && c1[i] > c0[i] && c1[i] > p0[i]) ? list[i] : -1;
+    for (int e = 0; e < 4; ++e)
+      if (g0 + (int64_t)(i0 + e) * kGrpThreads < np && c1[e] > c0[e] && c1[e] > p0[e]) list[i0 + e] = l[e];
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kGrpPer; ++i) rank[i] = list[i] >= 0 ? atomicAdd(&hist[list[i]], 1) : -1;
   __syncthreads();
+  if (gridDim.x == 1) {   // the block has seen every pair: ranks are final, and the counts are here
+    group_offsets(s, [&](int l) { return hist[l]; });
+#pragma unroll
+    for (int i = 0; i < kGrpPer; ++i) {
+      const int64_t g = g0 + (int64_t)i * kGrpThreads;
+      if (g < np) s.mf_pairs[g] = rank[i];
+    }
+    return;
+  }
   for (int l = threadIdx.x; l < s.nlist; l += kGrpThreads) {
     const int c = hist[l];
     if (c > 0) hist[l] = atomicAdd(&s.mf_cnt[l], c);
@@ -327,72 +414,6 @@ __global__ __launch_bounds__(kGrpThreads) void k_group_count(SearchDev s) {
   for (int i = 0; i < kGrpPer; ++i) {
     const int64_t g = g0 + (int64_t)i * kGrpThreads;
     if (g < np) s.mf_pairs[g] = list[i] >= 0 ? hist[list[i]] + rank[i] : -1;
-  }
-}
-
-// Single block: exclusive scans of pair counts and unit counts over lists
-// (thread t: a contiguous run of lists; wave scans, then the 16 wave totals);
-// resets the work counters.
-__global__ __launch_bounds__(kGrpThreads) void k_group_offsets(SearchDev s) {
-  __shared__ int64_t wp[kGrpThreads / kWave], wu[kGrpThreads / kWave];
-  constexpr int kPer = kMaxNlist / kGrpThreads;   // lists per thread, at most
-  static_assert(kMaxNlist % kGrpThreads == 0, "every list has a thread");
-  const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
-  if (t == 0) s.counters[2] = 0;
-  if (t < kScanSlices) s.counters[kScanSliceCtr + kScanSliceStride * t] = 0;
-  const int per = (s.nlist + kGrpThreads - 1) / kGrpThreads;
-  const int l0 = min(t * per, s.nlist), l1 = min(l0 + per, s.nlist);
-  const int rows = 16 * s.mf_rg;
-  auto units_of = [&](int c, int n) {
-    return c > 0 ? (int64_t)((n + s.chunk - 1) / s.chunk) * ((c + rows - 1) / rows) : (int64_t)0;
-  };
-  int c[kPer], n[kPer];
-  int64_t sp = 0, su = 0;
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    c[i] = n[i] = 0;
-    if (i >= per) continue;
-    const int l = min(l0 + i, s.nlist - 1);
-    c[i] = s.mf_cnt[l];
-    n[i] = s.list_off[l + 1] - s.list_off[l];
-  }
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    if (i >= per) continue;
-    c[i] = l0 + i < l1 ? c[i] : 0;
-    sp += c[i];
-    su += units_of(c[i], n[i]);
-  }
-  int64_t ip = sp, iu = su;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int64_t yp = __shfl_up(ip, o, kWave), yu = __shfl_up(iu, o, kWave);
-    ip += lane >= o ? yp : 0;
-    iu += lane >= o ? yu : 0;
-  }
-  if (lane == kWave - 1) {
-    wp[wave] = ip;
-    wu[wave] = iu;
-  }
-  __syncthreads();
-  int64_t bp = ip - sp, bu = iu - su, tp = 0, tu = 0;
-  for (int w = 0; w < kGrpThreads / kWave; ++w) {
-    bp += w < wave ? wp[w] : 0;
-    bu += w < wave ? wu[w] : 0;
-    tp += wp[w];
-    tu += wu[w];
-  }
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    if (i >= per || l0 + i >= l1) continue;
-    s.mf_pair_off[l0 + i] = bp;
-    s.mf_unit_off[l0 + i] = bu;
-    bp += c[i];
-    bu += units_of(c[i], n[i]);
-  }
-  if (t == 0) {
-    s.mf_pair_off[s.nlist] = tp;
-    s.mf_unit_off[s.nlist] = tu;
   }
 }
 
@@ -678,9 +699,9 @@ hipError_t launch_group_mfma(const SearchDev& s, hipStream_t st) {
   const int64_t np = s.nq * s.nprobe;
   const size_t shm = (size_t)s.nlist * sizeof(int32_t);   // at most 96 KiB (kMaxNlist)
   if (shm > 32768) allow_lds((const void*)k_group_count, shm);
-  hipLaunchKernelGGL(k_group_count, dim3((unsigned)((np + kGrpThreads * kGrpPer - 1) / (kGrpThreads * kGrpPer))),
-                     dim3(kGrpThreads), shm, st, s);
-  hipLaunchKernelGGL(k_group_offsets, dim3(1), dim3(kGrpThreads), 0, st, s);
+  const unsigned blocks = (unsigned)((np + kGrpThreads * kGrpPer - 1) / (kGrpThreads * kGrpPer));
+  hipLaunchKernelGGL(k_group_count, dim3(blocks), dim3(kGrpThreads), shm, st, s);
+  if (blocks > 1) hipLaunchKernelGGL(k_group_offsets, dim3(1), dim3(kGrpThreads), 0, st, s);
   hipLaunchKernelGGL(k_group_scatter, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, s);
   return hipGetLastError();
 }
