@@ -17,7 +17,7 @@
 //     per instruction, FP8 x FP4 at 64 and int8 at 64 per 64 dimensions, and
 //     the queries' fragments take 6 W registers instead of 8 W;
 //   - a lane owns one query (the output's column), so the query's constants
-//     sit in registers; the 32 codes' factors come from LDS by broadcast reads.
+//     sit in registers; the 32 codes' factors come from LDS by broadcast reads;
 // Per 32 x 32 block at W = 12 that is about 270 vector instructions where four
 // 16 x 16 int8 blocks took about 680.
 #include "rbq_internal.hpp"
@@ -42,11 +42,12 @@ typedef _Float16 f16x32 __attribute__((ext_vector_type(32)));
 // Operand layouts of v_mfma_scale_f32_32x32x64_f8f6f4 with FP4 A and FP6 B, as
 // measured on gfx950: lane l holds row (column) l % 32 and, in element e < 32,
 // k = 32 (l / 32) + e; output register i of lane l is row 8 (i / 4) + 4 (l / 32)
-// + i % 4 of column l % 32. Element e = 8 m + n of lane group g carries
-// dimension 64 t + 32 g + 4 n + m of code word t: nibble n of code dword
-// w & (0x11111111 << m) (m = 3: (w >> 1) & 0x44444444) is that dimension's bit
-// worth 0.5, 1, 2 or 2, and byte 8 m + n of the query row holds the dimension's
-// q_u times 0.5, 0.25, 0.125 or 0.125 (frag_pos, frag_scale: FP8 in memory).
+// + i % 4 of column l % 32. A K step takes 32 code bits w per lane (a half word);
+// element e = 8 m + n carries dimension 4 n + m of the half: nibble n of code
+// dword w & (0x11111111 << m) (m = 3: (w >> 1) & 0x44444444) is that dimension's
+// bit worth 0.5, 1, 2 or 2, and byte 8 m + n of the query's half word holds the
+// dimension's q_u times 0.5, 0.25, 0.125 or 0.125 (frag_pos, frag_scale: FP8 in
+// memory).
 
 // Wait states between the last product of a block and the first read of its
 // result. The compiler's own distance after a scaled product of mixed formats
@@ -72,8 +73,9 @@ __device__ __forceinline__ u32x6 fp6_fragment(const i32x4& lo, const i32x4& hi) 
   return __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(h, 1.0f);
 }
 
-// LDS of one wave: the block's 32 code factors {G, H, popcount, code term} and
-// the bounds of its 32 x 32 outputs ([register / 4][lane][register % 4]).
+// LDS of one wave: the block's 32 code factors {G, H, popcount, code term}, and
+// for the candidates of a block the bounds of its 32 x 32 outputs
+// ([register / 4][lane][register % 4]).
 struct WaveLds {
   float4 fac[32];
   float4 low[4][kWave];
@@ -87,93 +89,120 @@ struct Column {
   Cand* seg;
 };
 
+// A block of 32 codes as a lane loads it: lane group g takes both halves of
+// code words 2 p + g (one 8-byte load each; the two halves are the K steps 2 p
+// and 2 p + 1), and of an odd last word its half; the code's scan factors and
+// inner-product term.
+template <int WS>
+struct Block {
+  uint2 w[WS / 2 > 0 ? WS / 2 : 1];
+  uint32_t last;
+  float2 sf;
+  float fi;
+};
+
+// Next-unit hook of frag_unit: called once, early in the unit.
+struct NoHook {
+  __device__ __forceinline__ void operator()() const {}
+};
+
 // One unit on one wave: codes [start, start + n) of a list against the 32
 // queries whose fragments are fq. Candidates (bound without the pair term <=
 // thr) are appended to each column's segment in code order; returns how many
 // this lane's column has.
-template <bool DEBUG, int WS>
-__device__ int frag_unit(const SearchDev& s, int64_t start, int n, const Column& c, const u32x6 (&fq)[WS], WaveLds& L,
-                         const PairRec* rec, int32_t* dbg_ip, int32_t* dbg_pc, float* dbg_est, float* dbg_dist,
-                         float* dbg_lb, int64_t dbg_base) {
+// The next block's loads are issued before this block's products and waited for
+// before its candidates are stored: stores and loads share one in-order
+// counter, so a load waited for after them would wait for their completion too.
+template <bool DEBUG, int WS, class Hook>
+__device__ __forceinline__ int frag_unit(const SearchDev& s, int64_t start, int n, const Column& c, const u32x6 (&fq)[WS],
+                                         WaveLds& L, Hook hook, const PairRec* rec, int32_t* dbg_ip, int32_t* dbg_pc,
+                                         float* dbg_est, float* dbg_dist, float* dbg_lb, int64_t dbg_base) {
   const int lane = lane_id();
   const int col = lane & 31, grp = lane >> 5;
+  constexpr int NP = WS / 2;
   // wave-uniform bases (the unit's first 64-code row, its first factors) and
   // 32-bit byte offsets: position x = o0 + r of unit code r has word w at
   // ((x >> 6) W + w) 64 + (x & 63)
   const int o0 = (int)(start & 63);
   const char* cbase = reinterpret_cast<const char*>(s.codes) + (size_t)(start >> 6) * WS * 512;
+  const char* cbase4 = cbase + 4096;   // words 8..: within the loads' immediate offsets
   const char* sbase = reinterpret_cast<const char*>(s.sfac + start);
   const char* fbase = s.metric != 0 ? reinterpret_cast<const char*>(s.fip + start) : nullptr;
-  uint32_t cw[WS];
-  float2 sf;
-  float fi = 0.f;
-  // this lane's half of every word of its code (past the end: the last code,
-  // whose outputs are dropped), its factors and inner-product term
-  auto load = [&](int rb) {
+  // codes past the end load the last one; their outputs are dropped
+  auto load = [&](int rb, Block<WS>& k) {
     const uint32_t r = (uint32_t)min(rb + col, n - 1);
     const uint32_t x = (uint32_t)o0 + r;
-    const uint32_t wb = 8u * ((x >> 6) * (uint32_t)WS * 64u + (x & 63u)) + 4u * (uint32_t)grp;
+    const uint32_t wb = 8u * ((x >> 6) * (uint32_t)WS * 64u + (x & 63u));
+    const uint32_t wg = wb + 512u * (uint32_t)grp;
 #pragma unroll
-    for (int t = 0; t < WS; ++t) cw[t] = *reinterpret_cast<const uint32_t*>(cbase + (wb + 512u * (uint32_t)t));
-    sf = *reinterpret_cast<const float2*>(sbase + 8u * r);
-    if (fbase != nullptr) fi = *reinterpret_cast<const float*>(fbase + 4u * r);
+    for (int p = 0; p < NP; ++p)
+      k.w[p] = *reinterpret_cast<const uint2*>((p < 4 ? cbase : cbase4) + (wg + 1024u * (uint32_t)(p & 3)));
+    if constexpr (WS % 2 == 1)
+      k.last = *reinterpret_cast<const uint32_t*>((WS > 8 ? cbase4 : cbase) +
+                                                  (wb + 512u * (uint32_t)((WS - 1) & 7) + 4u * (uint32_t)grp));
+    k.sf = *reinterpret_cast<const float2*>(sbase + 8u * r);
+    if (fbase != nullptr) k.fi = *reinterpret_cast<const float*>(fbase + 4u * r);
   };
   int count = 0;
-  load(0);
-  for (int rb = 0; rb < n; rb += 32) {
+  auto block = [&](int rb, const Block<WS>& k, Block<WS>& next) {
+    if (rb + 32 < n) load(rb + 32, next);
     f32x16 acc;
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
     int pcp = 0;
-#pragma unroll
-    for (int t = 0; t < WS; ++t) {
-      const uint32_t w = cw[t];
+    auto step = [&](uint32_t w, int t) {
       pcp += __popc(w);
       const i32x8 a = {(int)(w & 0x11111111u), (int)(w & 0x22222222u), (int)(w & 0x44444444u),
                        (int)((w >> 1) & 0x44444444u), 0, 0, 0, 0};
       const i32x8 b = {(int)fq[t][0], (int)fq[t][1], (int)fq[t][2], (int)fq[t][3], (int)fq[t][4], (int)fq[t][5], 0, 0};
       // formats: A FP4 (4), B FP6 E2M3 (2); E8M0 scales 2^0 and 2^2
       acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 4, 2, 0, 127, 0, 129);
+    };
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      step(k.w[p].x, 2 * p);
+      step(k.w[p].y, 2 * p + 1);
     }
+    if constexpr (WS % 2 == 1) step(k.last, WS - 1);
     // the two lane groups hold the two halves of the code's bits
     const auto sw = __builtin_amdgcn_permlane32_swap((uint32_t)pcp, (uint32_t)pcp, false, false);
     const int pc = (int)(sw[0] + sw[1]);
     if (grp == 0) {
-      const float ct = fbase != nullptr ? -fi : code_term_l2(sf);
-      L.fac[col] = make_float4(sf.x, sf.y, (float)pc, ct);
+      const float ct = fbase != nullptr ? -k.fi : code_term_l2(k.sf);
+      L.fac[col] = make_float4(k.sf.x, k.sf.y, (float)pc, ct);
     }
     wave_lds_sync();
-    if (rb + 32 < n) load(rb + 32);   // in flight during this block's products and outputs
-    result_wait(acc);
+    const int left = n - rb;   // codes of the block that exist, if below 32
     // bounds without the pair term (as est_y / est_dl on the integer product);
     // fails: bit 15 - i is the sign of thr - bound of output i (two cheap
     // instructions without a lane mask between them). A NaN bound may count as
-    // passing: the rerank drops it.
-    // The factors are read four outputs ahead: left alone, the compiler reads
-    // each right before its use to save registers and waits 16 times.
+    // passing: the rerank drops it. The factors are read four outputs ahead:
+    // left alone, the compiler reads each right before its use to save registers
+    // and waits 16 times.
     float low[16];
     uint32_t fails = 0;
-    float4 fc[2][4];
+    float4 fc[2][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) fc[0][i] = L.fac[4 * grp + i];
+    for (int i = 0; i < 2; ++i) fc[0][i] = L.fac[4 * grp + i];
+    result_wait(acc);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      if ((i & 3) == 0 && i < 12) {
+      if ((i & 1) == 0 && i < 14) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) fc[(i >> 2) + 1 & 1][e] = L.fac[8 * (i >> 2) + 8 + 4 * grp + e];
+        for (int e = 0; e < 2; ++e) fc[((i >> 1) + 1) & 1][e] = L.fac[8 * ((i + 2) >> 2) + 4 * grp + ((i + 2) & 3) + e];
         asm volatile("" ::: "memory");
       }
-      const float4 f = fc[(i >> 2) & 1][i & 3];
+      const float4 f = fc[(i >> 1) & 1][i & 1];
       const float y = fmaf(c.a1, acc[i], fmaf(c.a2, f.z, c.a0));
       const float d0 = fmaf(f.x, y, f.w);
       low[i] = fmaf(c.coefh, f.y, d0);
       if constexpr (DEBUG) {
-        const int r = rb + 8 * (i >> 2) + 4 * grp + (i & 3);
-        if (col == 0 && r < n) {
-          const int64_t o = start + r - dbg_base;
+        const int code = 8 * (i >> 2) + 4 * grp + (i & 3);
+        if (col == 0 && code < left) {
+          const int64_t o = start + rb + code - dbg_base;
           dbg_ip[o] = (int)acc[i];
           dbg_pc[o] = (int)f.z;
-          dbg_est[o] = estimate_est(*rec, s.fac[start + r].y, (int)acc[i], (int)f.z);
+          dbg_est[o] = estimate_est(*rec, s.fac[start + rb + code].y, (int)acc[i], (int)f.z);
           dbg_dist[o] = d0 + c.pt;
           dbg_lb[o] = low[i] + c.pt;
         }
@@ -182,19 +211,30 @@ __device__ int frag_unit(const SearchDev& s, int64_t start, int n, const Column&
       }
     }
     if constexpr (!DEBUG) {
-      const uint32_t mask = ~fails & 0xFFFFu;
+      uint32_t mask = ~fails & 0xFFFFu;   // bit 15 - i: output i passes
+      if (left < 32) {   // the last block: codes past the end
+        const uint32_t v = ~(0xFFFFFFFFu >> left) << (4 * grp);   // this lane's codes: its nibbles from bit 31 down
+        mask &= ((v >> 16) & 0xF000u) | ((v >> 12) & 0x0F00u) | ((v >> 8) & 0x00F0u) | ((v >> 4) & 0x000Fu);
+      }
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        keep_loaded(next.w[p].x);
+        keep_loaded(next.w[p].y);
+      }
+      if constexpr (WS % 2 == 1) keep_loaded(next.last);
+      keep_loaded(next.sf.x);
+      keep_loaded(next.fi);
       if (__ballot(mask != 0u) != 0ull) {
         // the column's 32 codes in order, first code at bit 31: this lane's
         // groups of four between its partner's
         uint32_t sp = (mask | (mask << 8)) & 0x00FF00FFu;
         sp = (sp | (sp << 4)) & 0x0F0F0F0Fu;
         const auto pr = __builtin_amdgcn_permlane32_swap(sp, sp, false, false);
-        const int left = n - rb;   // codes of the block that exist
-        const uint32_t all = (((uint32_t)pr[0] << 4) | (uint32_t)pr[1]) & (left < 32 ? ~(0xFFFFFFFFu >> left) : ~0u);
-        // each lane's passing outputs one after the other (a few per lane)
+        const uint32_t all = ((uint32_t)pr[0] << 4) | (uint32_t)pr[1];
 #pragma unroll
         for (int j = 0; j < 4; ++j) L.low[j][lane] = make_float4(low[4 * j], low[4 * j + 1], low[4 * j + 2], low[4 * j + 3]);
         wave_lds_sync();
+        // each lane's passing outputs one after the other (a few per lane)
         uint32_t m = mask << 16;
         while (__ballot(m != 0u) != 0ull) {
           if (m != 0u) {
@@ -204,95 +244,105 @@ __device__ int frag_unit(const SearchDev& s, int64_t start, int n, const Column&
             Cand cd;
             cd.pos = (int32_t)start + rb + code;
             cd.lb = reinterpret_cast<const float*>(&L.low[i >> 2][lane])[i & 3] + c.pt;
-            if (code < left) c.seg[count + __popc(all & ~(0xFFFFFFFFu >> code))] = cd;
+            c.seg[count + __popc(all & ~(0xFFFFFFFFu >> code))] = cd;
           }
         }
         count += __popc(all);
       }
     }
-    wave_lds_sync();   // the next block's factors overwrite these
+    wave_lds_sync();   // the next block's values overwrite these
+  };
+  Block<WS> A, B;
+  load(0, A);
+  B = A;
+  hook();
+  for (int rb = 0; rb < n; rb += 64) {
+    block(rb, A, B);
+    if (rb + 32 < n) block(rb + 32, B, A);
   }
   return count;
 }
 
-// The list holding unit u: the largest l < n with off[l] <= u, by a 64-way
-// search (three rounds of loads for 16,384 lists).
-__device__ __forceinline__ int wave_find_list(const int64_t* __restrict__ off, int n, int64_t u) {
-  int lo = 0, hi = n;   // off[lo] <= u, and the list is in [lo, hi)
-  const int lane = lane_id();
-  while (hi - lo > 1) {
-    const int step = (hi - lo + kWave - 1) / kWave;
-    const int idx = lo + lane * step;
-    const bool ok = idx < hi && off[min(idx, n - 1)] <= u;
-    const uint64_t m = __ballot(ok);
-    const int j = 63 - __clzll((long long)m);   // lane 0 always holds (off[lo] <= u)
-    lo = uniform_i32(lo + j * step);
-    hi = min(hi, lo + step);
-  }
-  return lo;
-}
-
 template <int WS>
 __device__ __forceinline__ void load_fragments(const int8_t* row, int grp, u32x6 (&fq)[WS]) {
+  // K step t: half t % 2 of word t - t % 2 + grp; of an odd last word half grp
 #pragma unroll
   for (int t = 0; t < WS; ++t) {
-    const i32x4* p = reinterpret_cast<const i32x4*>(row + 64 * t + 32 * grp);
+    const i32x4* p = reinterpret_cast<const i32x4*>(
+        row + (t == WS - 1 && WS % 2 == 1 ? 64 * t + 32 * grp : 64 * (t - t % 2 + grp) + 32 * (t % 2)));
     fq[t] = fp6_fragment(p[0], p[1]);
   }
 }
 
-// Work units are (list, chunk of the list's codes, group of 32 pairs), ordered
-// by list, then chunk, then group, cut into kScanSlices contiguous slices; a
-// workgroup starts on the slice of its XCD (workgroups go to the XCDs in
-// turn), so the groups of one chunk run on one XCD and share its L2, then
-// moves on to the other slices. Each wave claims its units by itself.
+// Work units (MfUnit: list chunk x group of 32 pairs, ordered by list, then
+// chunk, then group) are cut into kScanSlices contiguous slices; a workgroup
+// starts on the slice of its XCD (workgroups go to the XCDs in turn), so the
+// groups of one chunk run on one XCD and share its L2, then moves on to the
+// other slices.
+struct Slices {
+  int64_t total;
+  int64_t lo, size, own;   // current slice: first unit, units, units given to its waves
+  unsigned long long* ctr;
+  int x0, j;
+  // The slice's first units belong to the waves that start on it, one each; the
+  // rest are claimed from its counter. A counter is only added to where it can
+  // have units left (4096 waves that each tried all eight took 100 us on their
+  // addresses).
+  __device__ __forceinline__ void open(const SearchDev& s) {
+    const int x = (x0 + j) % kScanSlices;
+    lo = total * x / kScanSlices;
+    size = total * (x + 1) / kScanSlices - lo;
+    own = (int64_t)kWaves * ((gridDim.x + kScanSlices - 1 - x) / kScanSlices);
+    ctr = s.counters + kScanSliceCtr + kScanSliceStride * x;
+  }
+  __device__ __forceinline__ uint32_t issue() const {   // a claim's ticket, in lane 0
+    uint32_t t = 0;
+    if (lane_id() == 0) t = (uint32_t)atomicAdd(ctr, 1ull);
+    return t;
+  }
+  // The unit of a ticket, or (slice exhausted) of a claim on the next slice
+  // that has one; -1: no unit is left.
+  __device__ __forceinline__ int64_t take(const SearchDev& s, int64_t at) {
+    for (;;) {
+      if (at < size) return lo + at;
+      for (;;) {
+        if (++j >= kScanSlices) return -1;
+        open(s);
+        const uint32_t seen = (uint32_t)__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (own + uniform_i32((int)seen) < size) break;
+      }
+      at = own + uniform_i32((int)issue());
+    }
+  }
+};
+
 template <int WS>
-__global__ __launch_bounds__(kThreads, WS <= 6 ? 4 : WS <= 12 ? 3 : 2) void k_scan_frag(SearchDev s) {
+__global__ __launch_bounds__(kThreads, WS <= 6 ? 4 : WS <= 12 && WS != 11 ? 3 : 2) void k_scan_frag(SearchDev s) {
   __shared__ WaveLds lds[kWaves];
   WaveLds& L = lds[threadIdx.x / kWave];
   const int lane = lane_id(), col = lane & 31, grp = lane >> 5;
-  const int64_t total = uniform_i64(s.mf_unit_off[s.nlist]);
-  const int x0 = (int)(blockIdx.x % kScanSlices);
-  for (int j = 0; j < kScanSlices; ++j) {
-    const int x = (x0 + j) % kScanSlices;
-    const int64_t lo = total * x / kScanSlices;
-    const int64_t size = total * (x + 1) / kScanSlices - lo;
-    // The slice's first units belong to the waves that start on it, one each; the
-    // rest are claimed from its counter. A counter is only added to where it can
-    // have units left (4096 waves that each tried all eight took 100 us on their
-    // addresses).
-    const int64_t own = (int64_t)kWaves * ((gridDim.x + kScanSlices - 1 - x) / kScanSlices);
-    unsigned long long* ctr = s.counters + kScanSliceCtr + kScanSliceStride * x;
-    int64_t next = -1;
-    if (j == 0) {
-      next = (int64_t)kWaves * (blockIdx.x / kScanSlices) + threadIdx.x / kWave;
-    } else {
-      const unsigned long long seen = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (own + uniform_i64((int64_t)seen) >= size) continue;
-    }
-    for (;;) {
-      if (next < 0) {
-        if (own >= size) break;
-        unsigned long long cl = 0;
-        if (lane == 0) cl = atomicAdd(ctr, 1ull);
-        next = own + uniform_i64((int64_t)cl);   // lane 0's claim (every lane is active)
-      }
-      if (next >= size) break;
-      const int64_t u = lo + uniform_i64(next);
-      next = -1;
-      const int list = wave_find_list(s.mf_unit_off, s.nlist, u);
-      const int local = (int)uniform_i64(u - s.mf_unit_off[list]);
-      const int64_t p0 = uniform_i64(s.mf_pair_off[list]);
-      const int cnt = (int)(uniform_i64(s.mf_pair_off[list + 1]) - p0);
-      const int ngroups = (cnt + 31) / 32;
-      const int ch = local / ngroups;
-      const int gi = local - ch * ngroups;
-      const int64_t lbeg = uniform_i32(s.list_off[list]), lend = uniform_i32(s.list_off[list + 1]);
-      const int64_t start = lbeg + (int64_t)ch * s.chunk;
-      const int n = (int)(min(lend, start + s.chunk) - start);
-      const MfRow row = s.mf_rows[p0 + min(32 * gi + col, cnt - 1)];
-      const bool live = 32 * gi + col < cnt && ch >= row.first;
-      if (__ballot(live) == 0ull) continue;   // every pair scanned this chunk in the bootstrap
+  Slices sl;
+  sl.total = uniform_i64(s.mf_unit_off[s.nlist]);
+  sl.x0 = (int)(blockIdx.x % kScanSlices);
+  sl.j = 0;
+  sl.open(s);
+  int64_t at = uniform_i64((int64_t)kWaves * (blockIdx.x / kScanSlices) + threadIdx.x / kWave);
+  int64_t u = sl.take(s, at);
+  while (u >= 0) {
+    const MfUnit un = s.mf_units[u];
+    const int64_t start = uniform_i32(un.start);
+    const int n = uniform_i32(un.n), slot = uniform_i32(un.slot), cr = uniform_i32(un.chunk_rows);
+    const int ch = cr >> 5, nrow = (cr & 31) + 1;
+    const MfRow row = s.mf_rows[slot + min(col, nrow - 1)];
+    const bool live = col < nrow && ch >= row.first;
+    // the next unit's claim travels while this one runs, unless the slice is
+    // about to end (a wave that holds a unit it has not begun delays the end)
+    const int64_t here = u - sl.lo;
+    const bool ahead = here + 2 * sl.own < sl.size;
+    uint32_t ticket = 0;
+    int64_t nu = -2;
+    if (ahead) ticket = sl.issue();
+    if (__ballot(live) != 0ull) {   // else every pair scanned this chunk in the bootstrap
       u32x6 fq[WS];
       load_fragments<WS>(s.qu8 + (int64_t)row.g * (64 * WS), grp, fq);
       Column c;
@@ -301,12 +351,22 @@ __global__ __launch_bounds__(kThreads, WS <= 6 ? 4 : WS <= 12 ? 3 : 2) void k_sc
       c.a0 = row.a0;
       c.coefh = row.coefh;
       c.pt = row.pt;
-      c.thr = live && row.thr == row.thr ? row.thr : -__builtin_inff();
+      c.thr = row.thr == row.thr ? row.thr : -__builtin_inff();
       c.seg = s.seg + row.seg + (int64_t)ch * s.chunk;
-      const int count = frag_unit<false, WS>(s, start, n, c, fq, L, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                             nullptr, 0);
+      if (!live) c.thr = -__builtin_inff();
+      const int count = frag_unit<false, WS>(s, start, n, c, fq, L, [&]() {
+        if (ahead) nu = sl.take(s, sl.own + uniform_i32((int)ticket));
+      }, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0);
       if (live && grp == 0) s.seg_count[row.count + ch] = count;
     }
+    if (nu == -2) {
+      if (!ahead) {
+        if (sl.own < sl.size) ticket = sl.issue();
+        else ticket = 0;   // nothing to claim on this slice: take() moves on
+      }
+      nu = sl.take(s, sl.own + uniform_i32((int)ticket));
+    }
+    u = nu;
   }
 }
 
@@ -332,7 +392,7 @@ __global__ __launch_bounds__(kWave) void k_debug_frag(SearchDev s, const PairRec
   c.pt = t.pt;
   c.thr = -__builtin_inff();
   c.seg = nullptr;
-  (void)frag_unit<true, WS>(s, start, (int)(end - start), c, fq, L, recp, ip, pc, est, dist, lb, lbeg);
+  (void)frag_unit<true, WS>(s, start, (int)(end - start), c, fq, L, NoHook{}, recp, ip, pc, est, dist, lb, lbeg);
 }
 
 template <bool DBG>

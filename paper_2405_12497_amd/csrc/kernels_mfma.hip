@@ -11,6 +11,7 @@
 // expands their bits to bytes in registers and issues one MFMA per 64
 // dimensions. Candidates (lb <= tau) are compacted per pair in code order, so
 // the segments are identical to those of the popcount scan.
+#include <algorithm>
 #include <type_traits>
 
 #include "rbq_internal.hpp"
@@ -417,9 +418,35 @@ __global__ __launch_bounds__(kGrpThreads) void k_group_count(SearchDev s) {
   }
 }
 
-// Every main-phase pair's record to its slot (after tau is known).
-__global__ __launch_bounds__(256) void k_group_scatter(SearchDev s) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The fragment scan's units, a thread per unit: its list by binary search over
+// the lists' unit offsets.
+__device__ __forceinline__ void group_units(const SearchDev& s, int block, int nblocks) {
+  const int64_t total = s.mf_unit_off[s.nlist];
+  for (int64_t u = (int64_t)block * blockDim.x + threadIdx.x; u < total; u += (int64_t)nblocks * blockDim.x) {
+    const int list = (int)(ub64(s.mf_unit_off, s.nlist + 1, u) - 1);
+    const int local = (int)(u - s.mf_unit_off[list]);
+    const int64_t p0 = s.mf_pair_off[list];
+    const int cnt = (int)(s.mf_pair_off[list + 1] - p0);
+    const int groups = (cnt + 31) / 32;
+    const int c = local / groups, gi = local - c * groups;
+    const int beg = s.list_off[list], len = s.list_off[list + 1] - beg;
+    MfUnit un;
+    un.start = beg + c * s.chunk;
+    un.n = min(s.chunk, len - c * s.chunk);
+    un.slot = (int32_t)p0 + 32 * gi;
+    un.chunk_rows = (c << 5) | (min(cnt - 32 * gi, 32) - 1);
+    s.mf_units[u] = un;
+  }
+}
+
+// Every main-phase pair's record to its slot (after tau is known); the first
+// unit_blocks blocks write the units.
+__global__ __launch_bounds__(256) void k_group_scatter(SearchDev s, int unit_blocks) {
+  if ((int)blockIdx.x < unit_blocks) {
+    group_units(s, blockIdx.x, unit_blocks);
+    return;
+  }
+  const int64_t g = (int64_t)(blockIdx.x - unit_blocks) * blockDim.x + threadIdx.x;
   if (g >= s.nq * s.nprobe) return;
   const int rank = s.mf_pairs[g];
   if (rank < 0) return;
@@ -702,7 +729,8 @@ hipError_t launch_group_mfma(const SearchDev& s, hipStream_t st) {
   const unsigned blocks = (unsigned)((np + kGrpThreads * kGrpPer - 1) / (kGrpThreads * kGrpPer));
   hipLaunchKernelGGL(k_group_count, dim3(blocks), dim3(kGrpThreads), shm, st, s);
   if (blocks > 1) hipLaunchKernelGGL(k_group_offsets, dim3(1), dim3(kGrpThreads), 0, st, s);
-  hipLaunchKernelGGL(k_group_scatter, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, s);
+  const int ub = s.frag ? (int)std::min<int64_t>(128, (np + 255) / 256) : 0;
+  hipLaunchKernelGGL(k_group_scatter, dim3((unsigned)(ub + (np + 255) / 256)), dim3(256), 0, st, s, ub);
   return hipGetLastError();
 }
 

@@ -68,6 +68,13 @@ struct MfRow {
   int64_t seg, count;
 };
 
+// A unit of the fragment scan: codes [start, start + n) of a list's chunk
+// against up to 32 of its pairs, records slot, slot + 1, ...
+struct MfUnit {
+  int32_t start, n, slot;
+  int32_t chunk_rows;   // chunk << 5 | pairs - 1
+};
+
 struct SeedEnt {
   float dist;
   int32_t id;   // original id (< 2^31), -1 for none
@@ -363,6 +370,7 @@ struct SearchDev {
   int64_t* mf_unit_off;     // nlist + 1: (chunk, 16 mf_rg pairs) units per list
   int32_t* mf_pairs;        // per pair: its rank among its list's main-phase pairs (-1: none)
   MfRow* mf_rows;           // the main-phase pairs' records by list
+  MfUnit* mf_units;         // the fragment scan's units
   // outputs
   int64_t* out_ids;
   float* out_d;

@@ -112,7 +112,7 @@ struct Workspace {
   DBuf chunk_qcode;   // chunk (query order) -> first query-code index
   DBuf q_boot, q_rerank, q_cand, nprobe_q, q_fb, feats, tmp;
   DBuf pair_pt, q_m, qn;    // inner-product metrics: pair constants, M_q, normalised queries (cosine)
-  DBuf mf_cnt, mf_pair_off, mf_unit_off, mf_pairs, mf_rows, units0, units1;
+  DBuf mf_cnt, mf_pair_off, mf_unit_off, mf_pairs, mf_rows, mf_units, units0, units1;
   DBuf fin_part, fin_pst;   // split rerank of small batches: partial top-k lists, statistics
   DBuf tau_part;            // split bootstrap rerank: exact keys, min(256, 4k) per query
 };

@@ -256,7 +256,7 @@ std::vector<DBuf*> rbq_index::all_buffers() {
           &ws.q_ncode, &ws.offs, &ws.counters, &ws.seg, &ws.seg_count, &ws.p0buf, &ws.tau,
           &ws.chunk_qcode,
           &ws.seedk, &ws.q_order, &ws.order_hist, &ws.lstats, &ws.q_boot, &ws.q_rerank, &ws.q_cand, &ws.pair_pt, &ws.q_m, &ws.qn, &ws.nprobe_q, &ws.q_fb, &ws.feats, &ws.tmp,
-          &ws.mf_cnt, &ws.mf_pair_off, &ws.mf_unit_off, &ws.mf_pairs, &ws.mf_rows, &ws.units0,
+          &ws.mf_cnt, &ws.mf_pair_off, &ws.mf_unit_off, &ws.mf_pairs, &ws.mf_rows, &ws.mf_units, &ws.units0,
           &ws.units1, &ws.fin_part, &ws.fin_pst, &ws.tau_part,
           &mlp.w32, &mlp.wbf, &mlp.wfrag, &mlp.grad, &mlp.m, &mlp.v, &mlp.act};
 }
@@ -664,10 +664,17 @@ rbq_status ensure_workspace(rbq_index* idx, int64_t nq, int nprobe, int k, int c
     HIPCHK(w.mf_pair_off.ensure((size_t)(idx->nlist + 1) * 8));
     HIPCHK(w.mf_unit_off.ensure((size_t)(idx->nlist + 1) * 8));
     HIPCHK(w.mf_pairs.ensure((size_t)np * 4));
-    // a record per pair with codes to scan (the batched scan's main phase has
-    // no unit table, which would take more: 80 bytes per chunk)
+    // a record per pair with codes to scan (with the units below less than the
+    // 80 bytes per chunk of a pair that the popcount scan's unit table takes)
     const int64_t nonempty = std::lower_bound(idx->sizes_desc.begin(), idx->sizes_desc.end(), (int64_t)0,
                                               std::greater<int64_t>()) - idx->sizes_desc.begin();
+    // units: at most one per chunk of a pair, and per list chunk one for each
+    // 32 pairs and a remainder
+    if (scan_frag_available(W, idx->prm.bq <= 4 ? 4 : 8)) {
+      const int64_t pair_chunks = nq * std::max<int64_t>(1, idx->max_chunks(nprobe, chunk));
+      HIPCHK(w.mf_units.ensure((size_t)std::min(pair_chunks, pair_chunks / 32 + idx->max_chunks(idx->nlist, chunk)) *
+                               sizeof(MfUnit)));
+    }
     HIPCHK(w.mf_rows.ensure((size_t)nq * std::max<int64_t>(1, std::min<int64_t>(nprobe, nonempty)) * sizeof(MfRow)));
   }
   HIPCHK(w.pair_choff.ensure((size_t)nq * (nprobe + 1) * 4));
@@ -773,6 +780,7 @@ SearchDev make_dev(rbq_index* idx, const float* queries, int64_t nq, int nprobe,
   s.mf_unit_off = (int64_t*)w.mf_unit_off.p;
   s.mf_pairs = (int32_t*)w.mf_pairs.p;
   s.mf_rows = (MfRow*)w.mf_rows.p;
+  s.mf_units = (MfUnit*)w.mf_units.p;
   s.units0 = (UnitDesc*)w.units0.p;
   s.units1 = (UnitDesc*)w.units1.p;
   s.chunk_qcode = (int32_t*)w.chunk_qcode.p;
