@@ -63,9 +63,11 @@ enum {
 
 /* Kernel that computes the integer <x_b, q_u> (Sec. 3.3.2). */
 enum {
-  RBQ_SCAN_AUTO = 0,     /* autotuned / heuristic choice per search */
+  RBQ_SCAN_AUTO = 0,     /* autotuned, else by batch size and code width */
   RBQ_SCAN_POPCNT = 1,   /* bit-plane AND + popcount, one code per lane */
-  RBQ_SCAN_MFMA = 2,     /* int8 MFMA over queries grouped by list */
+  RBQ_SCAN_MFMA = 2,     /* MFMA over queries grouped by list: FP6 (query) x FP4 (code
+                            bit) blocks, exact, for B_q <= 4 and codes up to 1024
+                            bits, int8 otherwise */
   RBQ_SCAN_MFMA_FP4 = 3  /* the same contraction on the scaled FP8 (query, E4M3) x
                             FP4 (code bit, E2M1) MFMA with FP32 accumulation, exact
                             for B_q <= 4 (RBQ_EUNSUPPORTED above) */

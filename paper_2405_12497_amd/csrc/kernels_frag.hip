@@ -176,7 +176,7 @@ __device__ __forceinline__ int frag_unit(const SearchDev& s, int64_t start, int 
     // bounds without the pair term (as est_y / est_dl on the integer product);
     // fails: bit 15 - i is the sign of thr - bound of output i (two cheap
     // instructions without a lane mask between them). A NaN bound may count as
-    // passing: the rerank drops it. The factors are read four outputs ahead:
+    // passing: the rerank drops it. The factors are read two outputs ahead:
     // left alone, the compiler reads each right before its use to save registers
     // and waits 16 times.
     float low[16];

@@ -69,7 +69,7 @@ void g_seg_budget_set(int64_t b);
 struct TuneEntry {
   int64_t max_nq = INT64_MAX;
   int chunk = kDefaultChunk;
-  int kernel = RBQ_SCAN_POPCNT;
+  int kernel = RBQ_SCAN_AUTO;   // AUTO: not tuned, auto_scan_kernel chooses
   int fin_w = 0;
   int mf_rg = 0;    // batched scan: 16-row query groups per work unit (0: one)
   float ms = 0.f;   // measured time of the trial batch

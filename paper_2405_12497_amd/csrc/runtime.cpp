@@ -962,6 +962,32 @@ rbq_status run_search(rbq_index* idx, const float* queries, int64_t nq, const rb
   return RBQ_OK;
 }
 
+// Scan kernel of an untuned search with scan_kernel = RBQ_SCAN_AUTO: the
+// fragment scan where enough queries share each list, else the popcount scan
+// (identical results). m = pairs per list: a 32 x 32 block of the fragment scan
+// costs the same for 1 or 32 queries, and grouping the pairs about 20 us a
+// search, so the line lies where the popcount scan's cost per code, which grows
+// with the code width, makes up for both. Measured on 200 to 300 codes per list
+// (popcount against fragment scan, us per search): W = 2, m = 16: 444 / 437, m =
+// 8: 289 / 318; W = 4, m = 32: 276 / 265, m = 16: 205 / 220; W = 5, m = 8: 258 /
+// 249, m = 4: 204 / 220; W = 8, m = 6: 283 / 271, m = 4: 243 / 248; W = 12, m =
+// 3: 429 / 379, m = 1: 280 / 299; W = 15, m = 4: 346 / 323, m = 2: 284 / 290.
+// Batches with little to scan (pairs x codes per list x words) don't earn the
+// grouping back, whatever m is. 64 lists of 1,562 codes, W = 12: 19 M words 227 /
+// 245, 77 M 374 / 319; W = 2: 13 M 164 / 198, 51 M 287 / 284; 256 lists of 781
+// codes, W = 7: 22 M 261 / 245; 512 lists of 39 codes, W = 5: 13 M 273 / 276 and
+// 230 / 216, 51 M 566 / 457. Lists shorter than a block's 32 codes leave it
+// mostly empty.
+int auto_scan_kernel(const rbq_index* idx, int64_t nq, double nprobe) {
+  if (!scan_frag_available(idx->W, idx->prm.bq <= 4 ? 4 : 8)) return RBQ_SCAN_POPCNT;
+  const int W = idx->W;
+  const double pairs = (double)nq * nprobe, m = pairs / idx->nlist;
+  const double line = W <= 1 ? 48 : W <= 4 ? 24 : W <= 7 ? 8 : W <= 11 ? 6 : 4;
+  const double codes = (double)idx->n / idx->nlist;
+  const double work = pairs * codes * W, least = W <= 4 ? 48e6 : 20e6;
+  return m >= line && codes >= 32 && work >= least ? RBQ_SCAN_MFMA : RBQ_SCAN_POPCNT;
+}
+
 // ------------------------------------------------------------------ graph replay
 namespace {
 constexpr size_t kMaxGraphs = 192;
@@ -1190,12 +1216,10 @@ rbq_status rbq::search_locked(rbq_index* idx, const float* queries, int64_t nq, 
   const int chunk = std::min(tc.chunk, kMaxP0 + 1 - o.k);   // bootstrap codes (k - 1 + chunk) fit the seed sort
   const int mf_rg = tc.mf_rg;
   if (o.rerank_waves == 0) o.rerank_waves = tc.fin_w;
-  if (kernel == RBQ_SCAN_AUTO || (kernel == RBQ_SCAN_MFMA && !rbq::mfma_available())) {
-    if (kernel == RBQ_SCAN_MFMA && o.scan_kernel == RBQ_SCAN_MFMA)
-      return fail(RBQ_EUNSUPPORTED, "the MFMA scan kernel is not available in this library");
-    kernel = RBQ_SCAN_POPCNT;
-  }
   const bool learned = !o.nprobe_per_query && o.use_learned_nprobe && idx->mlp.has_model;
+  // a per-query nprobe is about half its largest value on average
+  const bool choose = kernel == RBQ_SCAN_AUTO;
+  if (choose) kernel = auto_scan_kernel(idx, nq, o.nprobe * (learned || o.nprobe_per_query ? 0.5 : 1.0));
   // A query's candidate segment reserves a slot for each probed code, so a
   // batch is searched in sub-batches whose segments stay within kSegBudget
   // (same stream and workspace; queries keep their ids qid_base + i).
@@ -1263,6 +1287,14 @@ rbq_status rbq::search_locked(rbq_index* idx, const float* queries, int64_t nq, 
     rbq_status rs = graph ? rbq::search_graph(idx, qs, m, os, kernel, chunk, mf_rg, learned, oi, od, st, &npq, &stride)
                           : run_search(idx, qs, m, os, kernel, chunk, mf_rg, learned, oi, od, st, &npq, &stride,
                                        exact ? budget : 0, &m);
+    if (rs == RBQ_ENOMEM && choose && kernel == RBQ_SCAN_MFMA) {   // it takes a byte per pair and dimension more
+      kernel = RBQ_SCAN_POPCNT;
+      for (DBuf* b : {&idx->ws.qu8, &idx->ws.mf_pairs, &idx->ws.mf_rows, &idx->ws.mf_units}) b->release();
+      m = std::min(rows, nq - q0);
+      rs = graph ? rbq::search_graph(idx, qs, m, os, kernel, chunk, mf_rg, learned, oi, od, st, &npq, &stride)
+                 : run_search(idx, qs, m, os, kernel, chunk, mf_rg, learned, oi, od, st, &npq, &stride,
+                              exact ? budget : 0, &m);
+    }
     if (rs != RBQ_OK) return rs;
     if (stats) {
       rs = add_stats(m, npq, stride);

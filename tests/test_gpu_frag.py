@@ -1,0 +1,95 @@
+"""The fragment scan (batched, B_q <= 4, codes up to 16 words) against the
+popcount scan through the C ABI. Its products are integers below 2^24 summed in
+FP32 and its estimator is the popcount scan's arithmetic, so everything is
+equal: integers, estimates, bounds, candidate counts, reranks and results."""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# list lengths at the edges of its blocks (32 codes), code rows (64) and chunks (1024)
+SIZES = [0, 1, 31, 32, 33, 63, 64, 65, 95, 127, 129, 400, 1023, 1024, 1025, 1100]
+
+
+def _say(msg):
+    print(f"[{msg}]", flush=True)
+    sys.stdout.flush()
+
+
+def _index(dim, metric=0, seed=7, bq=4, sizes=SIZES):
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    rng = np.random.default_rng(dim * 31 + seed)
+    assign = np.repeat(np.arange(len(sizes)), sizes).astype(np.int32)
+    rng.shuffle(assign)
+    cent = rng.standard_normal((len(sizes), dim)).astype(np.float32) * 0.5
+    data = (cent[assign] + rng.standard_normal((len(assign), dim))).astype(np.float32)
+    idx = R.Index(dim, len(sizes), seed=seed, metric=metric, bq=bq)
+    idx.build(torch.from_numpy(data).cuda(), cent, assign)
+    return R, idx, data, cent, rng
+
+
+@pytest.mark.parametrize("words", range(1, 17))
+def test_scan_export_equals_popcount(words):
+    import torch
+    _say(f"export {words}")
+    R, idx, _, _, rng = _index(64 * words - 3)
+    qu = torch.from_numpy(rng.integers(0, 16, 64 * words).astype(np.uint8)).cuda()
+    for lst in (1, 2, 3, 4, 7, 12, 14):
+        n = SIZES[lst]
+        a = R.rbq_debug_scan(idx.h, lst, qu, 3.0, -0.07, 0.011, n, kernel=R.RBQ_SCAN_POPCNT)
+        for kern in (R.RBQ_SCAN_MFMA, R.RBQ_SCAN_MFMA_FP4):
+            b = R.rbq_debug_scan(idx.h, lst, qu, 3.0, -0.07, 0.011, n, kernel=kern)
+            for x, y in zip(a, b):
+                assert torch.equal(x, y), f"words {words} list of {n}"
+    idx.close()
+
+
+# rows per list around its groups of 32 queries, in every metric
+@pytest.mark.parametrize("words,nq,metric", [(1, 33, 0), (2, 1, 0), (2, 130, 1), (3, 31, 2), (4, 64, 0), (5, 65, 1),
+                                             (7, 32, 0), (8, 97, 2), (11, 40, 0), (12, 200, 0), (15, 33, 1), (16, 70, 0)])
+def test_search_equals_popcount(words, nq, metric):
+    import torch
+    _say(f"search {words} {nq} {metric}")
+    R, idx, data, cent, rng = _index(64 * words - 5, metric=metric)
+    q = torch.from_numpy((cent[rng.integers(0, len(cent), nq)] +
+                          rng.standard_normal((nq, data.shape[1]))).astype(np.float32)).cuda()
+    q[0] = torch.from_numpy(data[5]).cuda()      # at distance 0 of a code
+    q[-1] = torch.from_numpy(cent[4]).cuda()     # on a centroid: b = 0 for that list
+    npq = torch.from_numpy(rng.integers(1, 17, nq).astype(np.int32)).cuda()
+    for k, nprobe, extra in ((10, 16, {}), (1, 5, {}), (100, 16, {"nprobe_per_query": npq})):
+        a = idx.search(q, k, nprobe, scan_kernel=R.RBQ_SCAN_POPCNT, stats=True, **extra)
+        for kern in (R.RBQ_SCAN_MFMA, R.RBQ_SCAN_MFMA_FP4):
+            b = idx.search(q, k, nprobe, scan_kernel=kern, stats=True, **extra)
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and a[2] == b[2]
+    idx.close()
+
+
+def test_automatic_choice_equals_popcount():
+    """Shapes on both sides of the automatic choice's line, host and device buffers."""
+    import torch
+    _say("automatic choice")
+    rng = np.random.default_rng(3)
+    R, idx, data, cent, _ = _index(700, sizes=[70] * 1200)
+    for nq in (20, 400, 700):
+        q = (cent[rng.integers(0, len(cent), nq)] + rng.standard_normal((nq, 700))).astype(np.float32)
+        a = idx.search(torch.from_numpy(q).cuda(), 10, 24, scan_kernel=R.RBQ_SCAN_POPCNT, stats=True)
+        b = idx.search(torch.from_numpy(q).cuda(), 10, 24, stats=True)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and a[2] == b[2]
+        ids, dists, _ = idx.search(q, 10, 24)
+        assert np.array_equal(ids, a[0].cpu().numpy()) and np.array_equal(dists, a[1].cpu().numpy())
+        g = idx.search(torch.from_numpy(q).cuda(), 10, 24, use_graph=True)
+        g = idx.search(torch.from_numpy(q).cuda(), 10, 24, use_graph=True)
+        # a replay pads the batch, so an eager search of the same rows is the reference
+        assert torch.equal(g[0], a[0]) and torch.equal(g[1], a[1])
+    # queries that are not finite: no candidate of theirs survives, in either scan
+    q = rng.standard_normal((400, 700)).astype(np.float32)
+    q[3, 5] = np.nan
+    q[7, 1] = np.inf
+    q[9] = 1e30
+    a = idx.search(torch.from_numpy(q).cuda(), 10, 24, scan_kernel=R.RBQ_SCAN_POPCNT)
+    b = idx.search(torch.from_numpy(q).cuda(), 10, 24, scan_kernel=R.RBQ_SCAN_MFMA)
+    assert torch.equal(a[0], b[0]) and np.array_equal(a[1].cpu().numpy(), b[1].cpu().numpy(), equal_nan=True)
+    idx.close()
