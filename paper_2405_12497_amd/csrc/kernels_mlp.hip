@@ -175,6 +175,112 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const float* __restrict__ A, 
     }
 }
 
+// The same product for outputs too few to fill the chip with 64 x 64 tiles (the
+// weight gradients: 96 x 128 and 128 x 32 over K = batch rows). One 16 x 16 tile
+// per block of 16 waves: all waves fetch and round chunks of K into LDS in
+// fragment order, wave 0 runs the accumulation, one chain over K in the order of
+// k_gemm_bf16, so the sums are bit-equal to it. Bound by the latency of the
+// fetches: k_gemm_bf16 exposes it in every step of 32 (133 us for 96 x 128 x 4096
+// on its 4 blocks); 32 steps at a time, fetched without conditions and with the
+// next chunk's loads in flight during the products, take 15 us.
+constexpr int kDeepThreads = 1024, kDeepSteps = 32;   // K steps of 32 per chunk
+
+__global__ __launch_bounds__(kDeepThreads) void k_gemm_bf16_deep(const float* __restrict__ A, int64_t sam,
+                                                                 int64_t sak, const float* __restrict__ B,
+                                                                 int64_t sbk, int64_t sbn, float* __restrict__ C,
+                                                                 int64_t ldc, int M, int N, int K, int accumulate) {
+  __shared__ bf16x8 fa[2][kDeepSteps][kWave], fb[2][kDeepSteps][kWave];   // 128 KB
+  constexpr int per = kDeepSteps / (kDeepThreads / kWave);                // K steps per wave and chunk
+  const int wave = uniform_i32(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int fr = lane & 15, fk = (lane >> 4) * 8;
+  const int m = blockIdx.x * 16 + fr, n = blockIdx.y * 16 + fr;
+  const float* a = A + (int64_t)min(m, M - 1) * sam + fk * sak;
+  const float* b = B + (int64_t)min(n, N - 1) * sbn + fk * sbk;
+  const int steps = (K + 31) / 32;
+  float av[per][8], bv[per][8];
+  // Rows and columns beyond the operands repeat the last one: they only reach
+  // outputs that are not written. K beyond the operands is zeros.
+  auto load = [&](int s0) {
+    const int kw = (s0 + wave * per) * 32;
+    if (kw + per * 32 <= K) {
+      const float* aw = a + (int64_t)kw * sak;
+      const float* bw = b + (int64_t)kw * sbk;
+#pragma unroll
+      for (int j = 0; j < per; ++j)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          av[j][i] = aw[(j * 32 + i) * sak];
+          bv[j][i] = bw[(j * 32 + i) * sbk];
+        }
+    } else {
+#pragma unroll
+      for (int j = 0; j < per; ++j)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int64_t k = min(kw + j * 32 + fk + i, K - 1) - fk;
+          av[j][i] = a[k * sak];
+          bv[j][i] = b[k * sbk];
+        }
+    }
+  };
+  auto stage = [&](int s0, int buf) {
+    const int kw = (s0 + wave * per) * 32;
+    const bool full = kw + per * 32 <= K;
+#pragma unroll
+    for (int j = 0; j < per; ++j) {
+      if (!full) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (kw + j * 32 + fk + i >= K) av[j][i] = bv[j][i] = 0.f;
+      }
+      bf16x8 ua, ub;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {   // rounds as to_bf16, two values an instruction
+        ua[i] = (__bf16)av[j][i];
+        ub[i] = (__bf16)bv[j][i];
+      }
+      fa[buf][wave * per + j][lane] = ua;
+      fb[buf][wave * per + j][lane] = ub;
+    }
+  };
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (steps > 0) {
+    load(0);
+    stage(0, 0);
+  }
+  __syncthreads();
+  for (int s0 = 0, buf = 0; s0 < steps; s0 += kDeepSteps, buf ^= 1) {
+    const bool more = s0 + kDeepSteps < steps;
+    if (more) load(s0 + kDeepSteps);
+    if (wave == 0) {
+      const int c = min(kDeepSteps, steps - s0);
+      constexpr int G = 8;   // fragments read together
+      for (int j0 = 0; j0 < c; j0 += G) {
+        bf16x8 ga[G], gb[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+          ga[j] = fa[buf][j0 + j][lane];
+          gb[j] = fb[buf][j0 + j][lane];
+        }
+#pragma unroll
+        for (int j = 0; j < G; ++j)
+          if (j0 + j < c)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga[j], gb[j], acc, 0, 0, 0);
+      }
+    }
+    if (more) stage(s0 + kDeepSteps, buf ^ 1);
+    __syncthreads();
+  }
+  if (wave != 0 || n >= N) return;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int row = blockIdx.x * 16 + (lane >> 4) * 4 + e;
+    if (row >= M) continue;
+    float* c = C + (int64_t)row * ldc + n;
+    *c = accumulate ? *c + acc[e] : acc[e];
+  }
+}
+
 // ------------------------------------------------------------------ elementwise
 // A <- A + bias (pre-activation kept for the ReLU mask); H = max(A, 0).
 __global__ void k_bias_relu(float* __restrict__ A, const float* __restrict__ bias, float* __restrict__ H,
@@ -437,6 +543,14 @@ hipError_t launch_gemm_bf16(const float* A, int64_t sam, int64_t sak, const floa
                             hipStream_t st) {
   if (M <= 0 || N <= 0) return hipSuccess;
   dim3 grid((M + GT - 1) / GT, (N + GT - 1) / GT);
+  // Few tiles and a long K: k_gemm_bf16 takes 1.0 us per 32 of K whatever the
+  // tiles, k_gemm_bf16_deep 3.6 us per 1024; from 32 tiles on the chip is shared by
+  // enough of them that reading operands once per 64 rows pays.
+  if (grid.x * grid.y < 32 && K >= 512) {
+    hipLaunchKernelGGL(k_gemm_bf16_deep, dim3((M + 15) / 16, (N + 15) / 16), dim3(kDeepThreads), 0, st, A, sam, sak,
+                       B, sbk, sbn, C, ldc, M, N, K, accumulate ? 1 : 0);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_gemm_bf16, grid, dim3(256), 0, st, A, sam, sak, B, sbk, sbn, C, ldc, M, N, K,
                      accumulate ? 1 : 0);
   return hipGetLastError();

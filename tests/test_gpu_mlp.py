@@ -232,6 +232,40 @@ def test_gradients_match_reference():
         assert rel < 2e-2, name
 
 
+@pytest.mark.parametrize("n", [1, 16, 33, 65, 1023, 1024, 1025, 2049, 4100])
+def test_gradients_at_batch_edges(n):
+    """Batches around the GEMM's tiles, K steps and chunks, against FP64 with the
+    operands of each product rounded to BF16 as the kernels round them. What is
+    left is FP32 summation and operands that round the other way (2^-8 relative
+    each, few of them): below 2^-8 of a gradient's norm; one row lost of n would
+    be about 1 / sqrt(n), 1.6e-2 at the largest."""
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    _say(f"gradients of {n} rows")
+    rng = np.random.default_rng(n)
+    x = rng.normal(0, 1, (n, 96)).astype(np.float32)
+    y = rng.integers(0, 32, n).astype(np.int32)
+    w = _params(9).astype(np.float32)
+    loss, g = R.rbq_mlp_loss_grad(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(),
+                                  torch.from_numpy(w).cuda())
+    W1, b1, W2, b2 = M.split_params(w)
+    X, W1, W2 = bf16_round(x), bf16_round(W1), bf16_round(W2)
+    a = X @ W1 + b1
+    H = bf16_round(np.maximum(a, 0))
+    p = M.softmax(H @ W2 + b2)
+    oloss = -np.mean(np.log(p[np.arange(n), y]))
+    dz = p.copy()
+    dz[np.arange(n), y] -= 1.0
+    dz /= n
+    da = (bf16_round(dz) @ W2.T) * (a > 0)
+    want = (X.T @ bf16_round(da), da.sum(0), H.T @ bf16_round(dz), dz.sum(0))
+    assert loss == pytest.approx(oloss, rel=2.0 ** -8)
+    for name, gg, oo in zip(("W1", "b1", "W2", "b2"), M.split_params(g.cpu().numpy().astype(np.float64)), want):
+        rel = np.linalg.norm(gg - oo) / np.linalg.norm(oo)
+        print(f"grad {name} of {n} rows: relative norm error {rel:.2e}")
+        assert rel < 2.0 ** -8, name
+
+
 def test_training_fits_a_teacher():
     import torch
     from paper_2405_12497_amd import rabitq as R
