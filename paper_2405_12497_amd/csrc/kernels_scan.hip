@@ -738,7 +738,7 @@ __device__ __forceinline__ void acc4(float& acc, const float4& a, const float4& 
   acc1<IP>(acc, a.w, b.w);
 }
 
-template <int NC, int U = 1, bool IP = false>
+template <int NC, int U = 1, bool IP = false, bool QL = false>
 __device__ __forceinline__ void group_dists(const float* __restrict__ raw, const int32_t (&pos)[NC], int dim,
                                             const float* __restrict__ qv, int sub, float (&out)[NC], float mq = 0.f) {
   float acc[NC];
@@ -778,13 +778,14 @@ __device__ __forceinline__ void group_dists(const float* __restrict__ raw, const
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = min(i0 + u * kLpc + sub, n4 - 1);
-        b[u] = q4[i];
+        if constexpr (!QL) b[u] = q4[i];
 #pragma unroll
         for (int j = 0; j < NC; ++j) a[u][j] = reinterpret_cast<const float4*>(raw + base[j])[i];
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const bool live = i0 + u * kLpc + sub < n4;
+        if constexpr (QL) b[u] = q4[min(i0 + u * kLpc + sub, n4 - 1)];
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
           const float4 z = {0.f, 0.f, 0.f, 0.f};
@@ -798,13 +799,14 @@ __device__ __forceinline__ void group_dists(const float* __restrict__ raw, const
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = min(i0 + u * kLpc + sub, dim - 1);
-        b[u] = qv[i];
+        if constexpr (!QL) b[u] = qv[i];
 #pragma unroll
         for (int j = 0; j < NC; ++j) a[u][j] = raw[base[j] + i];
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const bool live = i0 + u * kLpc + sub < dim;
+        if constexpr (QL) b[u] = qv[min(i0 + u * kLpc + sub, dim - 1)];
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
           acc1<IP>(acc[j], live ? a[u][j] : (IP ? 0.f : b[u]), b[u]);
@@ -1009,25 +1011,107 @@ __device__ __forceinline__ int fin_lds_words(int k) { return kFinWin + kFinRound
 // of its chunks whose bound holds; it writes that top-k to part and
 // k_fin_merge keeps the k best distinct keys of the W lists (the seeds appear
 // in all of them).
-template <bool WIDE>
-__global__ __launch_bounds__(kThreads, WIDE ? 3 : 4) void k_finalize(SearchDev s, int W, uint64_t* __restrict__ part,
-                                                          int32_t* __restrict__ pst) {
+//
+// Bound by the fetches of raw vectors: at HBM rate where enough waves run (10,000
+// queries at D = 768, k = 10: 8.3 GB in 1.34 ms), by a share's chain of rounds
+// where one share is much longer than the rest. With CW > 1 a block of CW waves
+// takes one share: wave 0 gathers, chooses the rounds and merges as a single wave
+// would, all waves compute a round's distances, with the query in LDS and 2 to 4
+// times the fetches in flight.
+template <bool WIDE, int CW>
+__global__ __launch_bounds__(CW == 1 ? kThreads : CW * kWave, CW == 1 && !WIDE ? 4 : 3) void k_finalize(
+    SearchDev s, int W, uint64_t* __restrict__ part, int32_t* __restrict__ pst) {
   using DS = DistShape<WIDE>;
   extern __shared__ uint64_t fin_lds[];
-  const int wave = threadIdx.x >> 6, lane = lane_id();
+  __shared__ int32_t round_n;   // CW > 1: entries of the round, -1 when there is none left
+  const int wave = uniform_i32(threadIdx.x >> 6), lane = lane_id();
   if (s.prof_acc && blockIdx.x == 0 && threadIdx.x == 0) {   // codes estimated by each scan phase
     atomicAdd(&s.prof_acc[0], (unsigned long long)s.off_n0[s.nq]);
     atomicAdd(&s.prof_acc[1], (unsigned long long)(s.off_seg[s.nq] - s.off_n0[s.nq]));
   }
-  const int64_t wid = (int64_t)blockIdx.x * kWaves + wave;
+  const int64_t wid = CW == 1 ? (int64_t)blockIdx.x * kWaves + wave : (int64_t)blockIdx.x;
   if (wid >= s.nq * W) return;   // whole waves
   const int64_t qi = wid / W;
   const int64_t q = s.q_order ? (int64_t)uniform_i32(s.q_order[qi]) : qi;
   const int wsub = (int)(wid - qi * W);
   const int K = s.k;
-  uint64_t* win = fin_lds + (size_t)wave * fin_lds_words(K);
+  uint64_t* win = fin_lds + (CW == 1 ? (size_t)wave * fin_lds_words(K) : 0);
   uint64_t* rnd = win + kFinWin;
   uint64_t* top = rnd + kFinRoundMax;
+  const float* qg = s.q + q * s.dim;
+  float* ql = reinterpret_cast<float*>(top + K + (K & 1));   // CW > 1: the query, 16-byte aligned
+  if constexpr (CW > 1) {
+    for (int i = threadIdx.x; i < s.dim; i += CW * kWave) ql[i] = qg[i];
+    __syncthreads();
+  }
+  const float* qv = CW > 1 ? ql : qg;
+  const int grp = lane / kLpc, sub = lane % kLpc;
+  constexpr int kGroups = kWave / kLpc;
+
+  // exact distances of rnd[0..n) ((sortable bound << 32 | position) entries), in
+  // passes of NC entries a group (over the CW waves together); each entry becomes
+  // (distance << 32 | id)
+  auto pass = [&](int base, int n, auto nc_tag, auto u_tag) __attribute__((always_inline)) {
+    constexpr int NC = decltype(nc_tag)::value, U = decltype(u_tag)::value;
+    int32_t pos[NC];
+    const int i0 = base + (CW == 1 ? 0 : wave * kGroups) + grp;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int i = i0 + j * kGroups * CW;
+      pos[j] = (int32_t)(uint32_t)(rnd[min(i, n - 1)] & 0xffffffffu);
+      pos[j] = i < n ? pos[j] : -1;
+    }
+    // the ids travel with the raw vectors (one round trip for both)
+    uint32_t id[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) id[j] = id_lo32(s.ids, max(pos[j], 0));
+    float d[NC];
+    if (s.metric != 0) {
+      group_dists<NC, U, true, (CW > 1)>(s.raw, pos, s.dim, qv, sub, d, uniform_f32(s.q_m[q]));
+    } else {
+      group_dists<NC, U, false, (CW > 1)>(s.raw, pos, s.dim, qv, sub, d);
+    }
+#pragma unroll
+    for (int j = 0; j < NC; ++j) keep_loaded(id[j]);
+    wave_lds_sync();   // every lane has read its entries
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int i = i0 + j * kGroups * CW;
+      const uint64_t v = ((uint64_t)__float_as_uint(d[j]) << 32) | id[j];
+      if (sub == 0 && i < n) rnd[i] = v;
+    }
+    wave_lds_sync();
+  };
+  auto rerank = [&](int n) __attribute__((always_inline)) {
+    if constexpr (CW == 1) {
+      using UT = IntC<DS::kU>;
+      for (int base = 0; base < n; base += kGroups * DS::kMaxNC) {
+        const int per = (min(n - base, kGroups * DS::kMaxNC) + kGroups - 1) / kGroups;
+        if (per <= 1) pass(base, n, IntC<1>{}, UT{});
+        else if (per <= 2) pass(base, n, IntC<2>{}, UT{});
+        else if (per <= 4 || DS::kMaxNC == 4) pass(base, n, IntC<4>{}, UT{});
+        else pass(base, n, IntC<DS::kMaxNC>{}, UT{});
+      }
+    } else {
+      constexpr int kAll = kGroups * CW;   // entries per pass of NC = 1
+      if (wave * kGroups >= n) return;
+      constexpr int U = WIDE ? 8 : 4;
+      if (n <= kAll) pass(0, n, IntC<1>{}, IntC<U>{});
+      else if (n <= 2 * kAll) pass(0, n, IntC<2>{}, IntC<U>{});
+      else pass(0, n, IntC<(kFinRoundMax + kAll - 1) / kAll>{}, IntC<4>{});
+    }
+  };
+  if constexpr (CW > 1) {   // the other waves only take their share of each round
+    if (wave != 0) {
+      for (;;) {
+        __syncthreads();
+        const int n = round_n;
+        if (n < 0) return;
+        rerank(n);
+        __syncthreads();
+      }
+    }
+  }
   // seeds: the valid ones first, in (distance, id) order
   int cnt = 0;
   for (int i0 = 0; i0 < K; i0 += kWave) {
@@ -1044,9 +1128,6 @@ __global__ __launch_bounds__(kThreads, WIDE ? 3 : 4) void k_finalize(SearchDev s
   float tau = uniform_f32(cnt == K ? __uint_as_float((uint32_t)(top[K - 1] >> 32)) : __builtin_inff());
   const int seeds = cnt;
   int reranked = cnt, ncand = 0, nk = 0;
-  const float* qv = s.q + q * s.dim;
-  const int grp = lane / kLpc, sub = lane % kLpc;
-  constexpr int kGroups = kWave / kLpc;
 
   // rnd[0..n): (distance << 32 | id) of a round. Entries below the current
   // k-th (all of them while fewer than K are known) are compacted to the
@@ -1100,49 +1181,6 @@ __global__ __launch_bounds__(kThreads, WIDE ? 3 : 4) void k_finalize(SearchDev s
     if (cnt == K) tau = uniform_f32(fminf(tau, __uint_as_float((uint32_t)(top[K - 1] >> 32))));
   };
 
-  // exact distances of rnd[0..n) ((sortable bound << 32 | position) entries),
-  // in passes of 64: entry base + grp + 8 j, j < NC; each entry becomes
-  // (distance << 32 | id)
-  auto rerank = [&](int n) {
-    auto pass = [&](int base, auto nc_tag) {
-      constexpr int NC = decltype(nc_tag)::value;
-      int32_t pos[NC];
-#pragma unroll
-      for (int j = 0; j < NC; ++j) {
-        const int i = base + grp + j * kGroups;
-        pos[j] = (int32_t)(uint32_t)(rnd[min(i, n - 1)] & 0xffffffffu);
-        pos[j] = i < n ? pos[j] : -1;
-      }
-      // the ids travel with the raw vectors (one round trip for both)
-      uint32_t id[NC];
-#pragma unroll
-      for (int j = 0; j < NC; ++j) id[j] = id_lo32(s.ids, max(pos[j], 0));
-      float d[NC];
-      if (s.metric != 0) {
-        group_dists<NC, DS::kU, true>(s.raw, pos, s.dim, qv, sub, d, uniform_f32(s.q_m[q]));
-      } else {
-        group_dists<NC, DS::kU, false>(s.raw, pos, s.dim, qv, sub, d);
-      }
-#pragma unroll
-      for (int j = 0; j < NC; ++j) keep_loaded(id[j]);
-      wave_lds_sync();   // every lane has read its entries
-#pragma unroll
-      for (int j = 0; j < NC; ++j) {
-        const int i = base + grp + j * kGroups;
-        const uint64_t v = ((uint64_t)__float_as_uint(d[j]) << 32) | id[j];
-        if (sub == 0 && i < n) rnd[i] = v;
-      }
-      wave_lds_sync();
-    };
-    for (int base = 0; base < n; base += kGroups * DS::kMaxNC) {
-      const int per = (min(n - base, kGroups * DS::kMaxNC) + kGroups - 1) / kGroups;
-      if (per <= 1) pass(base, IntC<1>{});
-      else if (per <= 2) pass(base, IntC<2>{});
-      else if (per <= 4 || DS::kMaxNC == 4) pass(base, IntC<4>{});
-      else pass(base, IntC<DS::kMaxNC>{});
-    }
-  };
-
   auto process_window = [&]() {
     while (nk > 0) {
       uint32_t cut = 0xFFFFFFFFu;
@@ -1176,7 +1214,14 @@ __global__ __launch_bounds__(kThreads, WIDE ? 3 : 4) void k_finalize(SearchDev s
       if (nr == 0) break;   // no live entry at or below the cut: none is live at all
       wave_lds_sync();
       reranked += nr;
-      rerank(nr);
+      if constexpr (CW > 1) {
+        if (lane == 0) round_n = nr;
+        __syncthreads();
+        rerank(nr);
+        __syncthreads();
+      } else {
+        rerank(nr);
+      }
       merge(nr);
     }
     nk = 0;
@@ -1241,6 +1286,10 @@ __global__ __launch_bounds__(kThreads, WIDE ? 3 : 4) void k_finalize(SearchDev s
     }
   }
   process_window();
+  if constexpr (CW > 1) {
+    if (lane == 0) round_n = -1;
+    __syncthreads();
+  }
   if (W == 1) {
     const float mq = s.metric != 0 ? s.q_m[q] : 0.f;
     for (int i = lane; i < K; i += kWave) {
@@ -1486,6 +1535,18 @@ int finalize_split(int64_t nq, int k) {
 }
 
 namespace {
+// Waves that rerank together for each of a query's W shares (the order of its
+// rounds, and so the results, is the same): one where the shares fill the chip
+// evenly, kFinBlockWaves where a share of one or two lists makes the longest much
+// longer than the mean, or there are too few shares. 256 queries at D = 960, k =
+// 100, 8 lists over W = 8: 950 us / 590 us (mean of a share 100 us, longest 950);
+// 64 shares: 21 / 18 us at D = 768, 12.1 / 10.5 us at D = 128; even shares: 500
+// queries at D = 128, 40 lists over W = 4: 27 / 39 us, 1000 at D = 300, 48 over 2:
+// 163 / 172 us.
+constexpr int kFinBlockWaves = 4;
+int finalize_waves(int64_t units, int W, int nprobe) {
+  return W > 1 && (units <= 512 || nprobe <= 2 * W) ? kFinBlockWaves : 1;
+}
 constexpr int kOrderBins = 64;
 
 __global__ void k_zero_i32(int32_t* __restrict__ p, int64_t n) {   // a kernel, not a memset: capturable
@@ -1538,12 +1599,25 @@ hipError_t launch_query_order(const int32_t* nprobe_q, int64_t nq, int nprobe, i
 hipError_t launch_finalize_split(const SearchDev& s, int W, uint64_t* part, int32_t* pst, hipStream_t st) {
   if (s.nq <= 0) return hipSuccess;
   if (W < 1 || (W > 1 && (!part || !pst || W * s.k > kFinMergeCap))) return hipErrorInvalidValue;
-  const size_t shm = (size_t)kWaves * (kFinWin + kFinRoundMax + s.k) * sizeof(uint64_t);
-  const dim3 grid((unsigned)((s.nq * W + kWaves - 1) / kWaves));
+  const int cw = finalize_waves(s.nq * W, W, s.nprobe);
+  const size_t shm = (size_t)(cw == 1 ? kWaves : 1) * (kFinWin + kFinRoundMax + s.k + (s.k & 1)) * sizeof(uint64_t) +
+                     (cw == 1 ? 0 : (size_t)s.dim * sizeof(float));
+  const dim3 grid((unsigned)(cw == 1 ? (s.nq * W + kWaves - 1) / kWaves : s.nq * W));
+  auto run = [&](auto wide, auto cwt) {
+    constexpr int CW = decltype(cwt)::value;
+    constexpr bool WIDE = decltype(wide)::value != 0;
+    hipLaunchKernelGGL((k_finalize<WIDE, CW>), grid, dim3(CW == 1 ? kThreads : CW * kWave), shm, st, s, W, part, pst);
+  };
+  auto pick = [&](auto wide) {
+    if (cw == 1)
+      run(wide, IntC<1>{});
+    else
+      run(wide, IntC<kFinBlockWaves>{});
+  };
   if (dist_wide(s.dim))
-    hipLaunchKernelGGL(k_finalize<true>, grid, dim3(kThreads), shm, st, s, W, part, pst);
+    pick(IntC<1>{});
   else
-    hipLaunchKernelGGL(k_finalize<false>, grid, dim3(kThreads), shm, st, s, W, part, pst);
+    pick(IntC<0>{});
   if (W > 1 && W * s.k > kMergeWaveMax)
     hipLaunchKernelGGL(k_fin_merge_block, dim3((unsigned)s.nq), dim3(kMergeThreads), 0, st, s, W, part, pst);
   else if (W > 1)

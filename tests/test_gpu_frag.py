@@ -93,3 +93,28 @@ def test_automatic_choice_equals_popcount():
     b = idx.search(torch.from_numpy(q).cuda(), 10, 24, scan_kernel=R.RBQ_SCAN_MFMA)
     assert torch.equal(a[0], b[0]) and np.array_equal(a[1].cpu().numpy(), b[1].cpu().numpy(), equal_nan=True)
     idx.close()
+
+
+@pytest.mark.parametrize("dim,k,metric", [(30, 1, 0), (128, 100, 0), (255, 10, 1), (260, 33, 0), (771, 10, 2), (1027, 64, 0)])
+def test_block_rerank_equals_wave_rerank(dim, k, metric):
+    """A query's rerank shares by one wave each (a large batch of many lists) and
+    by a block of waves each (few shares; shares of one or two lists): the rounds
+    are the same, so are ids, distances and counts."""
+    import torch
+    _say(f"rerank {dim} {k} {metric}")
+    R, idx, data, cent, rng = _index(dim, metric=metric, sizes=[40, 0, 700, 1500, 64, 3, 300, 260, 900, 128])
+    q = torch.from_numpy((cent[rng.integers(0, len(cent), 400)] +
+                          rng.standard_normal((400, dim))).astype(np.float32)).cuda()
+    q[1] = torch.from_numpy(data[5]).cuda()
+    for waves, nprobe in ((2, 10), (4, 9)):
+        kw = dict(rerank_waves=waves, scan_kernel=R.RBQ_SCAN_POPCNT, stats=True)
+        a = idx.search(q, k, nprobe, **kw)                # 800 or more shares of several lists
+        b = idx.search(q[:100], k, nprobe, **kw)          # at most 400 shares
+        assert torch.equal(a[0][:100], b[0]) and torch.equal(a[1][:100], b[1])
+        c = idx.search(q, k, 2 * waves, **kw)             # shares of two lists
+        d = [idx.search(q[i:i + 1], k, 2 * waves, qid_base=i, **kw) for i in range(0, 400, 16)]
+        assert torch.equal(c[0][::16], torch.cat([x[0] for x in d]))
+        assert torch.equal(c[1][::16], torch.cat([x[1] for x in d]))
+        e = idx.search(q[:8], k, nprobe, rerank_waves=1, scan_kernel=R.RBQ_SCAN_POPCNT, stats=True)
+        assert e[2]["candidates"] == idx.search(q[:8], k, nprobe, **kw)[2]["candidates"]
+    idx.close()
