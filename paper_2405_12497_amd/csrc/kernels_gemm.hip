@@ -376,18 +376,16 @@ void launch_f32_mfma(const float* A, int64_t lda, const float* sub, const int32_
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
-typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint16_t f2bf(float x) {   // round to nearest even
-  uint32_t u = __float_as_uint(x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 constexpr int BK = 32;
 
-template <int T>
+// VEC: K and lda are multiples of 8 and 4 (a thread's EPT consecutive k are all
+// inside or all outside the row): 16-byte loads without conditions, rows beyond M
+// and N repeat the last one (their outputs are not written), k beyond K is zeroed
+// in A when stashed. The general form loads single elements, each waited for
+// under its own condition: 10,000 x 768 x 768 took 237 us with it, 73 us with VEC
+// and a second LDS buffer (one barrier per step).
+template <int T, bool VEC>
 __global__ __launch_bounds__(256) void k_gemm_bf16x3(const float* __restrict__ A, int64_t lda,
                                                      const float* __restrict__ sub,
                                                      const int32_t* __restrict__ sel,
@@ -399,8 +397,8 @@ __global__ __launch_bounds__(256) void k_gemm_bf16x3(const float* __restrict__ A
   constexpr int TPR = BK / EPT;       // threads per tile row
   constexpr int WB = T / 32;          // 16x16 blocks per wave and dimension
   // k-contiguous rows, padded by 8 elements so 16-byte reads stay aligned
-  __shared__ __attribute__((aligned(16))) uint16_t Ah[T][BK + 8], Al[T][BK + 8];
-  __shared__ __attribute__((aligned(16))) uint16_t Bh[T][BK + 8], Bl[T][BK + 8];
+  __shared__ __attribute__((aligned(16))) uint16_t Ah[2][T][BK + 8], Al[2][T][BK + 8];
+  __shared__ __attribute__((aligned(16))) uint16_t Bh[2][T][BK + 8], Bl[2][T][BK + 8];
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
   const int64_t m0 = (int64_t)blockIdx.x * T;
@@ -419,9 +417,42 @@ __global__ __launch_bounds__(256) void k_gemm_bf16x3(const float* __restrict__ A
   // B loader: n row tid / TPR, EPT consecutive k
   const int lb_n = tid / TPR, lb_k = (tid % TPR) * EPT;
   const int bn = n0 + lb_n;
+  typedef uint16_t u16xe __attribute__((ext_vector_type(EPT)));
+  typedef __bf16 bf16xe __attribute__((ext_vector_type(EPT)));
+  const float* avr = A + min(am, M - 1) * lda;
+  const float* svr = sel ? sub + (int64_t)sel[min(am, M - 1)] * K : nullptr;
+  const int64_t bo = (int64_t)min(bn, N - 1) * K;
   float av[EPT];
-  uint16_t bhv[EPT], blv[EPT];
+  u16xe bhv, blv;
   auto fetch = [&](int k0) {
+    if constexpr (VEC) {
+      const int ka = min(k0 + la_k, K - EPT), kb = min(k0 + lb_k, K - EPT);
+      float4 v[EPT / 4];
+#pragma unroll
+      for (int i = 0; i < EPT / 4; ++i) v[i] = *reinterpret_cast<const float4*>(avr + ka + 4 * i);
+      bhv = *reinterpret_cast<const u16xe*>(Bhi + bo + kb);
+      blv = *reinterpret_cast<const u16xe*>(Blo + bo + kb);
+      if (svr) {
+        float4 c[EPT / 4];
+#pragma unroll
+        for (int i = 0; i < EPT / 4; ++i) c[i] = *reinterpret_cast<const float4*>(svr + ka + 4 * i);
+#pragma unroll
+        for (int i = 0; i < EPT / 4; ++i) {
+          v[i].x -= c[i].x;
+          v[i].y -= c[i].y;
+          v[i].z -= c[i].z;
+          v[i].w -= c[i].w;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < EPT / 4; ++i) {
+        av[4 * i] = v[i].x;
+        av[4 * i + 1] = v[i].y;
+        av[4 * i + 2] = v[i].z;
+        av[4 * i + 3] = v[i].w;
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < EPT; ++i) {
       const int kk = k0 + la_k + i;
@@ -431,67 +462,39 @@ __global__ __launch_bounds__(256) void k_gemm_bf16x3(const float* __restrict__ A
         if (srow) v -= srow[kk];
       }
       av[i] = v;
-    }
-#pragma unroll
-    for (int i = 0; i < EPT; ++i) bhv[i] = blv[i] = 0;
-    if (bn < N) {
-      const int64_t o = (int64_t)bn * K + k0 + lb_k;
-      if constexpr (EPT == 8) {
-        if (k0 + lb_k + 8 <= K && (o & 7) == 0) {
-          const u16x8 h = *reinterpret_cast<const u16x8*>(Bhi + o);
-          const u16x8 l = *reinterpret_cast<const u16x8*>(Blo + o);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            bhv[i] = h[i];
-            blv[i] = l[i];
-          }
-          return;
-        }
-      } else {
-        if (k0 + lb_k + 4 <= K && (o & 3) == 0) {
-          const u16x4 h = *reinterpret_cast<const u16x4*>(Bhi + o);
-          const u16x4 l = *reinterpret_cast<const u16x4*>(Blo + o);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            bhv[i] = h[i];
-            blv[i] = l[i];
-          }
-          return;
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) {
-        if (k0 + lb_k + i < K) {
-          bhv[i] = Bhi[o + i];
-          blv[i] = Blo[o + i];
-        }
-      }
+      bhv[i] = bn < N && k0 + lb_k + i < K ? Bhi[bo + k0 + lb_k + i] : (uint16_t)0;
+      blv[i] = bn < N && k0 + lb_k + i < K ? Blo[bo + k0 + lb_k + i] : (uint16_t)0;
     }
   };
-  auto stash = [&]() {
+  auto stash = [&](int k0, int buf) {
+    bf16xe h, l;
+    const bool in = !VEC || k0 + la_k < K;
 #pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-      const uint16_t h = f2bf(av[i]);
-      Ah[la_r][la_k + i] = h;
-      Al[la_r][la_k + i] = f2bf(av[i] - bf2f(h));
-      Bh[lb_n][lb_k + i] = bhv[i];
-      Bl[lb_n][lb_k + i] = blv[i];
+    for (int i = 0; i < EPT; ++i) {   // hardware conversions, round to nearest even
+      const float v = in ? av[i] : 0.f;
+      h[i] = (__bf16)v;
+      l[i] = (__bf16)(v - (float)h[i]);
     }
+    *reinterpret_cast<bf16xe*>(&Ah[buf][la_r][la_k]) = h;
+    *reinterpret_cast<bf16xe*>(&Al[buf][la_r][la_k]) = l;
+    *reinterpret_cast<u16xe*>(&Bh[buf][lb_n][lb_k]) = bhv;
+    *reinterpret_cast<u16xe*>(&Bl[buf][lb_n][lb_k]) = blv;
   };
   fetch(0);
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    stash();
-    __syncthreads();
-    if (k0 + BK < K) fetch(k0 + BK);   // in flight during this step's MFMAs
+  stash(0, 0);
+  __syncthreads();
+  for (int k0 = 0, buf = 0; k0 < K; k0 += BK, buf ^= 1) {
+    const bool more = k0 + BK < K;
+    if (more) fetch(k0 + BK);   // in flight during this step's MFMAs
     // operand fragments: row (or column) lane%16, k = (lane/16)*8 .. +7
     const int fr = lane & 15, fk = (lane >> 4) * 8;
     bf16x8 ah[WB], al[WB], bh2[WB], bl2[WB];
 #pragma unroll
     for (int i = 0; i < WB; ++i) {
-      ah[i] = *reinterpret_cast<const bf16x8*>(&Ah[wm + i * 16 + fr][fk]);
-      al[i] = *reinterpret_cast<const bf16x8*>(&Al[wm + i * 16 + fr][fk]);
-      bh2[i] = *reinterpret_cast<const bf16x8*>(&Bh[wn + i * 16 + fr][fk]);
-      bl2[i] = *reinterpret_cast<const bf16x8*>(&Bl[wn + i * 16 + fr][fk]);
+      ah[i] = *reinterpret_cast<const bf16x8*>(&Ah[buf][wm + i * 16 + fr][fk]);
+      al[i] = *reinterpret_cast<const bf16x8*>(&Al[buf][wm + i * 16 + fr][fk]);
+      bh2[i] = *reinterpret_cast<const bf16x8*>(&Bh[buf][wn + i * 16 + fr][fk]);
+      bl2[i] = *reinterpret_cast<const bf16x8*>(&Bl[buf][wn + i * 16 + fr][fk]);
     }
 #pragma unroll
     for (int i = 0; i < WB; ++i)
@@ -501,6 +504,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16x3(const float* __restrict__ A
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl2[j], acc[i][j], 0, 0, 0);
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh2[j], acc[i][j], 0, 0, 0);
       }
+    if (more) stash(k0 + BK, buf ^ 1);   // the other buffer: last read before the previous barrier
     __syncthreads();
   }
   // output fragment: column lane%16, rows (lane/16)*4 + 0..3
@@ -592,7 +596,7 @@ __global__ __launch_bounds__(256) void k_cd_bf16x3(const float* __restrict__ A, 
     auto& Al = Ts[buf][1];
     auto& Bh = Ts[buf][2];
     auto& Bl = Ts[buf][3];
-    // hardware conversions, round to nearest even (as f2bf)
+    // hardware conversions, round to nearest even
     bf16x8 h[2], l[2];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -746,13 +750,12 @@ hipError_t launch_gemm_bf16x3(const float* A, int64_t lda, const float* sub, con
                               const uint16_t* Bhi, const uint16_t* Blo, float* Y, int64_t ldy,
                               int64_t M, int N, int K, hipStream_t st) {
   if (M <= 0) return hipSuccess;
-  if (((M + 63) / 64) * (((int64_t)N + 63) / 64) >= 256) {
-    dim3 grid((unsigned)((M + 63) / 64), (N + 63) / 64);
-    hipLaunchKernelGGL(k_gemm_bf16x3<64>, grid, dim3(256), 0, st, A, lda, sub, sel, Bhi, Blo, Y, ldy, M, N, K);
-  } else {
-    dim3 grid((unsigned)((M + 31) / 32), (N + 31) / 32);
-    hipLaunchKernelGGL(k_gemm_bf16x3<32>, grid, dim3(256), 0, st, A, lda, sub, sel, Bhi, Blo, Y, ldy, M, N, K);
-  }
+  const bool vec = (K & 7) == 0 && (lda & 3) == 0;
+  const int T = ((M + 63) / 64) * (((int64_t)N + 63) / 64) >= 256 ? 64 : 32;
+  const dim3 grid((unsigned)((M + T - 1) / T), (N + T - 1) / T);
+  auto kern = T == 64 ? (vec ? k_gemm_bf16x3<64, true> : k_gemm_bf16x3<64, false>)
+                      : (vec ? k_gemm_bf16x3<32, true> : k_gemm_bf16x3<32, false>);
+  hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, A, lda, sub, sel, Bhi, Blo, Y, ldy, M, N, K);
   return hipGetLastError();
 }
 
