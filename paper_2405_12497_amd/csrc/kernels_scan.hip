@@ -1549,50 +1549,51 @@ int finalize_waves(int64_t units, int W, int nprobe) {
 }
 constexpr int kOrderBins = 64;
 
-__global__ void k_zero_i32(int32_t* __restrict__ p, int64_t n) {   // a kernel, not a memset: capturable
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
 __device__ __forceinline__ int order_bin(int npq, int nprobe) {
   return min(kOrderBins - 1, (int)((int64_t)min(max(npq, 1), nprobe) * kOrderBins / (nprobe + 1)));
 }
 
-__global__ void k_order_hist(const int32_t* __restrict__ npq, int64_t nq, int nprobe, int32_t* hist) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < nq) atomicAdd(&hist[order_bin(npq[q], nprobe)], 1);
-}
-
-// One wave: hist[b] -> the first slot of bin b, bins in descending order.
-__global__ void k_order_scan(int32_t* hist) {
-  const int lane = threadIdx.x;   // kOrderBins == kWave
-  const int b = kOrderBins - 1 - lane;   // lane 0 holds the heaviest bin
-  const int c = hist[b];
-  int inc = c;
+// The queries in descending order of their nprobe's bin, by one block: a
+// histogram per wave in LDS, the first slot of every (bin, wave), then the same
+// queries again to their slots. Bound by the LDS atomics of equal bins, which one
+// block serves in 15 us for 10,000 queries; counters in memory took 230 us, 10,000
+// atomics on 64 addresses each way.
+constexpr int kOrderThreads = 1024, kOrderWaves = kOrderThreads / kWave;
+__global__ __launch_bounds__(kOrderThreads) void k_query_order(const int32_t* __restrict__ npq, int64_t nq, int nprobe,
+                                                               int32_t* __restrict__ order) {
+  __shared__ int32_t at[kOrderWaves][kOrderBins];
+  const int wave = threadIdx.x >> 6, lane = lane_id();
+  at[wave][lane] = 0;
+  wave_lds_sync();
+  for (int64_t q = threadIdx.x; q < nq; q += kOrderThreads) atomicAdd(&at[wave][order_bin(npq[q], nprobe)], 1);
+  __syncthreads();
+  if (wave == 0) {
+    const int b = kOrderBins - 1 - lane;   // lane 0 holds the heaviest bin
+    int c = 0;
+    for (int w = 0; w < kOrderWaves; ++w) c += at[w][b];
+    int inc = c;
 #pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int y = __shfl_up(inc, o, kWave);
-    if (lane >= o) inc += y;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int y = __shfl_up(inc, o, kWave);
+      if (lane >= o) inc += y;
+    }
+    int first = inc - c;
+    for (int w = 0; w < kOrderWaves; ++w) {
+      const int n = at[w][b];
+      at[w][b] = first;
+      first += n;
+    }
   }
-  hist[kOrderBins + b] = inc - c;
-}
-
-__global__ void k_order_scatter(const int32_t* __restrict__ npq, int64_t nq, int nprobe, int32_t* hist,
-                                int32_t* __restrict__ order) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q < nq) order[atomicAdd(&hist[kOrderBins + order_bin(npq[q], nprobe)], 1)] = (int32_t)q;
+  __syncthreads();
+  for (int64_t q = threadIdx.x; q < nq; q += kOrderThreads)
+    order[atomicAdd(&at[wave][order_bin(npq[q], nprobe)], 1)] = (int32_t)q;
 }
 }  // namespace
 
-hipError_t launch_query_order(const int32_t* nprobe_q, int64_t nq, int nprobe, int32_t* hist, int32_t* order,
-                              hipStream_t st) {
+hipError_t launch_query_order(const int32_t* nprobe_q, int64_t nq, int nprobe, int32_t* order, hipStream_t st) {
   static_assert(kOrderBins == kWave, "one lane per bin");
   if (nq <= 0) return hipSuccess;
-  const unsigned g = (unsigned)((nq + 255) / 256);
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(2 * kOrderBins), 0, st, hist, (int64_t)(2 * kOrderBins));
-  hipLaunchKernelGGL(k_order_hist, dim3(g), dim3(256), 0, st, nprobe_q, nq, nprobe, hist);
-  hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(kWave), 0, st, hist);
-  hipLaunchKernelGGL(k_order_scatter, dim3(g), dim3(256), 0, st, nprobe_q, nq, nprobe, hist, order);
+  hipLaunchKernelGGL(k_query_order, dim3(1), dim3(kOrderThreads), 0, st, nprobe_q, nq, nprobe, order);
   return hipGetLastError();
 }
 

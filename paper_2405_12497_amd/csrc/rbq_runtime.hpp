@@ -107,7 +107,7 @@ uint64_t host_splitmix64(uint64_t x);
 struct Workspace {
   DBuf qrot, cd, cgmin, probe, probe_d, pairs, planes, qu8, pair_choff, pair_codeoff;
   DBuf q_nch, q_p0, q_n0, q_ncode, offs, counters, seg, seg_count, p0buf, tau, seedk;
-  DBuf q_order, order_hist;   // rerank query order (per-query nprobe)
+  DBuf q_order;   // rerank query order (per-query nprobe)
   DBuf lstats;                // learned nprobe: statistics of each query's 8 nearest lists
   DBuf chunk_qcode;   // chunk (query order) -> first query-code index
   DBuf q_boot, q_rerank, q_cand, nprobe_q, q_fb, feats, tmp;

@@ -255,7 +255,7 @@ std::vector<DBuf*> rbq_index::all_buffers() {
           &ws.planes, &ws.qu8, &ws.pair_choff, &ws.pair_codeoff, &ws.q_nch, &ws.q_p0, &ws.q_n0,
           &ws.q_ncode, &ws.offs, &ws.counters, &ws.seg, &ws.seg_count, &ws.p0buf, &ws.tau,
           &ws.chunk_qcode,
-          &ws.seedk, &ws.q_order, &ws.order_hist, &ws.lstats, &ws.q_boot, &ws.q_rerank, &ws.q_cand, &ws.pair_pt, &ws.q_m, &ws.qn, &ws.nprobe_q, &ws.q_fb, &ws.feats, &ws.tmp,
+          &ws.seedk, &ws.q_order, &ws.lstats, &ws.q_boot, &ws.q_rerank, &ws.q_cand, &ws.pair_pt, &ws.q_m, &ws.qn, &ws.nprobe_q, &ws.q_fb, &ws.feats, &ws.tmp,
           &ws.mf_cnt, &ws.mf_pair_off, &ws.mf_unit_off, &ws.mf_pairs, &ws.mf_rows, &ws.mf_units, &ws.units0,
           &ws.units1, &ws.fin_part, &ws.fin_pst, &ws.tau_part,
           &mlp.w32, &mlp.wbf, &mlp.wfrag, &mlp.grad, &mlp.m, &mlp.v, &mlp.act};
@@ -952,9 +952,7 @@ rbq_status run_search(rbq_index* idx, const float* queries, int64_t nq, const rb
   s.prof_acc = pf.on ? (unsigned long long*)pf.acc.p : nullptr;   // codes counted by finalize
   if (nprobe_q) {   // uneven reranks: the largest nprobe first
     HIPCHK(idx->ws.q_order.ensure((size_t)nq * 4));
-    HIPCHK(idx->ws.order_hist.ensure(128 * 4));
-    HIPCHK(launch_query_order(nprobe_q, nq, o.nprobe, (int32_t*)idx->ws.order_hist.p, (int32_t*)idx->ws.q_order.p,
-                              st));
+    HIPCHK(launch_query_order(nprobe_q, nq, o.nprobe, (int32_t*)idx->ws.q_order.p, st));
     s.q_order = (const int32_t*)idx->ws.q_order.p;
   }
   HIPCHK(launch_finalize_split(s, fin_w, (uint64_t*)idx->ws.fin_part.p, (int32_t*)idx->ws.fin_pst.p, st));
