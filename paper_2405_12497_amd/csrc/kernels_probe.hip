@@ -481,6 +481,10 @@ __global__ __launch_bounds__(kSelThreads) void k_select_probe_grp(const float* _
     total += tot;
   }
   if (total <= kGrpSelCap) {
+    if (total > 256) {
+      wave_keep_smallest(sel, total, P);
+      total = P;
+    }
     wave_sort_sel(sel, total);
   } else {
     wave_lds_sync();   // the group list is no longer read

@@ -853,45 +853,51 @@ __device__ __forceinline__ uint32_t sortable_bits(float x) {
 // best of them by (distance, id) seed the top-k and tau = the k-th. The others
 // cannot enter the top-k (k better ones are known), so all m segment entries
 // are marked done (pos = -1).
-// With W > 1 (small batches, large k), W waves share a query: each makes the
-// same selection, reranks its share [m w / W, m (w + 1) / W) of it and writes
-// those exact keys to tpart (stride min(kMaxK, 4k) per query); k_tau_merge
-// sorts them and writes the seeds and tau.
-template <bool WIDE>
-__global__ __launch_bounds__(kThreads) void k_tau(SearchDev s, int W, uint64_t* __restrict__ tpart) {
+// BLOCK: a block of kWaves waves per query: wave 0 selects and sorts, all compute
+// distances, twice the columns in flight. A single wave's round trips bound small
+// batches: 256 queries at D = 960, k = 100, 134 us before (eight waves per query,
+// each selecting, and a merge kernel) and 80 us now; 333 at D = 768, k = 10, 27.6
+// and 21.7 us. From kTauBlock queries on, single waves fill the chip and HBM bounds
+// both (10,000 at D = 768: 1.2 GB in 273 us).
+constexpr int64_t kTauBlock = 2048;
+template <bool WIDE, bool BLOCK>
+__global__ __launch_bounds__(kThreads) void k_tau(SearchDev s) {
   using DS = DistShape<WIDE>;
-  __shared__ uint64_t selw[kWaves][kWSelCap];
-  const int wave = threadIdx.x >> 6, lane = lane_id();
-  const int64_t wid = (int64_t)blockIdx.x * kWaves + wave;
-  if (wid >= s.nq * W) return;   // whole waves
-  const int64_t q = wid / W;
-  const int wsub = (int)(wid - q * W);
-  uint64_t* sel = selw[wave];
+  __shared__ uint64_t selw[BLOCK ? 1 : kWaves][kWSelCap];
+  const int wave = uniform_i32(threadIdx.x >> 6), lane = lane_id();
+  const int64_t q = BLOCK ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kWaves + wave;
+  if (q >= s.nq) return;   // whole waves
+  const bool lead = !BLOCK || wave == 0;
+  uint64_t* sel = selw[BLOCK ? 0 : wave];
   const int n0 = uniform_i32(s.q_n0[q]);
   const int64_t b0 = uniform_i64(s.off_n0[q]);
-  const int mstride = min(kMaxK, 4 * s.k);
-  const int m = min(n0, mstride);
-  const int lo = (int)((int64_t)m * wsub / W), hi = (int)((int64_t)m * (wsub + 1) / W);
-  if (wsub == 0 && lane == 0) s.q_boot[q] = m;   // exact distances of the bootstrap rerank
+  const int m = min(n0, min(kMaxK, 4 * s.k));
+  if (lead && lane == 0) s.q_boot[q] = m;   // exact distances of the bootstrap rerank
   if (m > 0) {
     const EstEnt* est = s.p0buf + b0;
-    wave_smallest<8, kMaxP0 / kWave>([&](int i) { return __float_as_uint(est[i].dist); },
-                                     [](uint32_t v) { return sortable_bits(__uint_as_float(v)); }, n0, m, sel);
+    if (lead)
+      wave_smallest<8, kMaxP0 / kWave>([&](int i) { return __float_as_uint(est[i].dist); },
+                                       [](uint32_t v) { return sortable_bits(__uint_as_float(v)); }, n0, m, sel);
+    if constexpr (BLOCK) __syncthreads();
     const int64_t seg0 = uniform_i64(s.off_seg[q]);
     const float* qv = s.q + q * s.dim;
     const int grp = lane / kLpc, sub = lane % kLpc;
     constexpr int kGroups = kWave / kLpc;
-    // passes over the wave's share [lo, hi): entry base + grp + 8 j, j < NC (a
-    // bootstrap entry's index is its slot in the query's segment)
-    auto run = [&](int base, auto nc_tag) {
-      constexpr int NC = decltype(nc_tag)::value;
+    // passes over the m entries: entry base + grp + 8 j, j < NC, the block's waves 8
+    // entries apart (a bootstrap entry's index is its slot in the query's segment)
+    constexpr int kStep = BLOCK ? kGroups * kWaves : kGroups;
+    auto run = [&](int base, auto nc_tag, auto u_tag) {
+      constexpr int NC = decltype(nc_tag)::value, U = decltype(u_tag)::value;
+      const int i0 = base + grp + (BLOCK ? wave * kGroups : 0);
       int32_t slot[NC], pos[NC];
       // clamped reads, then masks: reads under per-entry branches would each
       // wait at the branch's join
 #pragma unroll
       for (int j = 0; j < NC; ++j) {
-        const int i = base + grp + j * kGroups;
-        slot[j] = (int32_t)(uint32_t)(sel[min(i, hi - 1)] & 0xffffffffu);
+        const int i = i0 + j * kStep;
+        slot[j] = (int32_t)(uint32_t)(sel[min(i, m - 1)] & 0xffffffffu);
+        // another wave may have replaced that last entry already
+        if (BLOCK) slot[j] = i < m ? slot[j] : 0;
       }
 #pragma unroll
       for (int j = 0; j < NC; ++j) pos[j] = est[slot[j]].pos;
@@ -899,7 +905,7 @@ __global__ __launch_bounds__(kThreads) void k_tau(SearchDev s, int W, uint64_t* 
       for (int j = 0; j < NC; ++j) keep_loaded(pos[j]);
 #pragma unroll
       for (int j = 0; j < NC; ++j) {
-        const bool in = base + grp + j * kGroups < hi;
+        const bool in = i0 + j * kStep < m;
         slot[j] = in ? slot[j] : -1;
         pos[j] = in ? pos[j] : -1;
       }
@@ -909,63 +915,47 @@ __global__ __launch_bounds__(kThreads) void k_tau(SearchDev s, int W, uint64_t* 
       for (int j = 0; j < NC; ++j) id[j] = id_lo32(s.ids, max(pos[j], 0));
       float d[NC];
       if (s.metric != 0) {
-        group_dists<NC, DS::kU, true>(s.raw, pos, s.dim, qv, sub, d, uniform_f32(s.q_m[q]));
+        group_dists<NC, U, true>(s.raw, pos, s.dim, qv, sub, d, uniform_f32(s.q_m[q]));
       } else {
-        group_dists<NC, DS::kU, false>(s.raw, pos, s.dim, qv, sub, d);
+        group_dists<NC, U, false>(s.raw, pos, s.dim, qv, sub, d);
       }
 #pragma unroll
       for (int j = 0; j < NC; ++j) keep_loaded(id[j]);
       wave_lds_sync();   // every lane has read its sel entries
 #pragma unroll
       for (int j = 0; j < NC; ++j) {
-        const int i = base + grp + j * kGroups;
+        const int i = i0 + j * kStep;
         // exact distances are >= 0, so their bits order like the values; ids < 2^31
         const uint64_t v = ((uint64_t)__float_as_uint(d[j]) << 32) | id[j];
-        if (sub == 0 && i < hi) {
+        if (sub == 0 && i < m) {
           s.seg[seg0 + slot[j]].pos = -1;
           sel[i] = v;
         }
       }
       wave_lds_sync();
     };
-    for (int base = lo; base < hi; base += kGroups * DS::kMaxNC) {
-      const int per = (min(hi - base, kGroups * DS::kMaxNC) + kGroups - 1) / kGroups;
-      if (per <= 1) run(base, IntC<1>{});
-      else if (per <= 2) run(base, IntC<2>{});
-      else if (per <= 4 || DS::kMaxNC == 4) run(base, IntC<4>{});
-      else run(base, IntC<DS::kMaxNC>{});
-    }
-    if (W > 1) {
-      for (int i = lo + lane; i < hi; i += kWave) tpart[q * mstride + i] = sel[i];
-      return;
+    if constexpr (BLOCK) {
+      constexpr int U = WIDE ? 8 : 4;
+      for (int base = 0; base + wave * kGroups < m; base += 2 * kStep) {
+        if (m - base <= kStep) run(base, IntC<1>{}, IntC<U>{});
+        else run(base, IntC<2>{}, IntC<U>{});
+      }
+      __syncthreads();
+      if (wave != 0) return;
+    } else {
+      using UT = IntC<DS::kU>;
+      for (int base = 0; base < m; base += kGroups * DS::kMaxNC) {
+        const int per = (min(m - base, kGroups * DS::kMaxNC) + kGroups - 1) / kGroups;
+        if (per <= 1) run(base, IntC<1>{}, UT{});
+        else if (per <= 2) run(base, IntC<2>{}, UT{});
+        else if (per <= 4 || DS::kMaxNC == 4) run(base, IntC<4>{}, UT{});
+        else run(base, IntC<DS::kMaxNC>{}, UT{});
+      }
     }
     wave_sort_sel(sel, m);
-  } else if (W > 1) {
-    return;   // the merge writes the empty seeds
+  } else if (!lead) {
+    return;   // wave 0 writes the empty seeds
   }
-  for (int i = lane; i < s.k; i += kWave) {
-    SeedEnt e;
-    const bool live = i < min(m, s.k);
-    const uint64_t v = live ? sel[i] : 0;
-    e.dist = live ? __uint_as_float((uint32_t)(v >> 32)) : __builtin_inff();
-    e.id = live ? (int32_t)(uint32_t)(v & 0xffffffffu) : -1;
-    s.seedk[q * s.k + i] = e;
-  }
-  if (lane == 0) s.tau[q] = (m >= s.k) ? __uint_as_float((uint32_t)(sel[s.k - 1] >> 32)) : __builtin_inff();
-}
-
-// The seeds and tau of a query whose bootstrap rerank was shared by several
-// waves: its m exact keys from tpart, sorted.
-__global__ __launch_bounds__(kThreads) void k_tau_merge(SearchDev s, const uint64_t* __restrict__ tpart) {
-  __shared__ uint64_t selw[kWaves][kMaxK];
-  const int wave = threadIdx.x >> 6, lane = lane_id();
-  const int64_t q = (int64_t)blockIdx.x * kWaves + wave;
-  if (q >= s.nq) return;   // whole waves
-  uint64_t* sel = selw[wave];
-  const int mstride = min(kMaxK, 4 * s.k);
-  const int m = min(uniform_i32(s.q_n0[q]), mstride);
-  for (int i = lane; i < m; i += kWave) sel[i] = tpart[q * mstride + i];
-  if (m > 0) wave_sort_sel(sel, m);
   for (int i = lane; i < s.k; i += kWave) {
     SeedEnt e;
     const bool live = i < min(m, s.k);
@@ -1367,8 +1357,25 @@ __global__ __launch_bounds__(kThreads) void k_fin_merge(SearchDev s, int W, cons
   fin_merge_out(s, q, W, sel, n, pst);
 }
 
-// More keys (up to kFinMergeCap): one block per query sorts them in LDS.
+// Minimum over the wave, in every lane's hands (a scalar).
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+  auto step = [&](auto ctrl, auto rows) {
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)0xFFFFFFFF, (int)v, decltype(ctrl)::value,
+                                                     decltype(rows)::value, 0xf, false));
+  };
+  step(IntC<0x111>{}, IntC<0xf>{});   // row_shr 1, 2, 4, 8
+  step(IntC<0x112>{}, IntC<0xf>{});
+  step(IntC<0x114>{}, IntC<0xf>{});
+  step(IntC<0x118>{}, IntC<0xf>{});
+  step(IntC<0x142>{}, IntC<0xa>{});   // row_bcast 15, 31
+  step(IntC<0x143>{}, IntC<0xc>{});
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
 constexpr int kMergeThreads = 512;
+// More results than kMergeHeadsMax: one block per query sorts the keys in LDS (8
+// lists of 100: 18.9 us, 25 us as a chain).
+constexpr int kMergeHeadsMax = 64;
 __global__ __launch_bounds__(kMergeThreads) void k_fin_merge_block(SearchDev s, int W,
                                                                    const uint64_t* __restrict__ part,
                                                                    const int32_t* __restrict__ pst) {
@@ -1381,6 +1388,46 @@ __global__ __launch_bounds__(kMergeThreads) void k_fin_merge_block(SearchDev s, 
   __syncthreads();
   bitonic_sort_u64(sel, n2);
   if (threadIdx.x < kWave) fin_merge_out(s, q, W, sel, n, pst);
+}
+
+// More keys (up to kFinMergeCap) of at most 64 lists: lane w of one wave holds the
+// head of (sorted) list w, and each of the k results is the smallest head, taken
+// off every list that holds it (the seeds are in all of them). Bound by that chain,
+// 0.2 us a result: 64 lists of 10 keys take 4.4 us, 16 us sorted by a block.
+__global__ __launch_bounds__(kMergeThreads) void k_fin_merge_heads(SearchDev s, int W,
+                                                                   const uint64_t* __restrict__ part,
+                                                                   const int32_t* __restrict__ pst) {
+  __shared__ uint64_t sel[kFinMergeCap];
+  __shared__ uint64_t top[kMergeHeadsMax];
+  const int64_t q = blockIdx.x;
+  const int K = s.k, n = W * K, lane = lane_id();
+  for (int i = threadIdx.x; i < n; i += kMergeThreads) sel[i] = part[q * n + i];
+  __syncthreads();
+  if (threadIdx.x >= kWave) return;
+  const uint64_t* mine = sel + min(lane, W - 1) * K;
+  uint64_t head = lane < W ? mine[0] : ~0ull, next = lane < W && K > 1 ? mine[1] : ~0ull;
+  uint64_t last = ~0ull;
+  int at = 0, out = 0;
+  while (out < K) {
+    const uint32_t h = wave_min_u32((uint32_t)(head >> 32));
+    if (h == 0xFFFFFFFFu) break;   // every list is used up
+    const bool tied = (uint32_t)(head >> 32) == h;
+    const uint64_t b = __ballot(tied);
+    const int first = __builtin_ctzll(b);
+    uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)head, first);
+    if (__ballot(tied && (uint32_t)head != l)) l = wave_min_u32(tied ? (uint32_t)head : 0xFFFFFFFFu);
+    const uint64_t key = (uint64_t)h << 32 | l;
+    if (lane == 0) top[out] = key;
+    out += out == 0 || key != last;   // distinct keys
+    last = key;
+    if (tied && (uint32_t)head == l) {
+      head = next;
+      ++at;
+      next = at + 1 < K ? mine[at + 1] : ~0ull;
+    }
+  }
+  wave_lds_sync();
+  fin_merge_out(s, q, W, top, out, pst);
 }
 
 // ------------------------------------------------------------------ debug
@@ -1505,26 +1552,15 @@ hipError_t launch_plan(const SearchDev& s, hipStream_t st) {
 }
 
 
-int tau_split(int fin_w, int k) {
-  const int m = std::min(kMaxK, 4 * k);
-  return std::max(1, std::min(fin_w, m / 32));   // at least 32 entries per wave
-}
-
-hipError_t launch_tau_split(const SearchDev& s, int W, uint64_t* tpart, hipStream_t st) {
+hipError_t launch_tau(const SearchDev& s, hipStream_t st) {
   if (s.nq <= 0) return hipSuccess;
-  if (W < 1 || (W > 1 && !tpart)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((s.nq * W + kWaves - 1) / kWaves));
-  if (dist_wide(s.dim))
-    hipLaunchKernelGGL(k_tau<true>, grid, dim3(kThreads), 0, st, s, W, tpart);
-  else
-    hipLaunchKernelGGL(k_tau<false>, grid, dim3(kThreads), 0, st, s, W, tpart);
-  if (W > 1)
-    hipLaunchKernelGGL(k_tau_merge, dim3((unsigned)((s.nq + kWaves - 1) / kWaves)), dim3(kThreads), 0, st, s,
-                       tpart);
+  const bool block = s.nq < kTauBlock;
+  const dim3 grid((unsigned)(block ? s.nq : (s.nq + kWaves - 1) / kWaves));
+  auto kern = dist_wide(s.dim) ? (block ? k_tau<true, true> : k_tau<true, false>)
+                               : (block ? k_tau<false, true> : k_tau<false, false>);
+  hipLaunchKernelGGL(kern, grid, dim3(kThreads), 0, st, s);
   return hipGetLastError();
 }
-
-hipError_t launch_tau(const SearchDev& s, hipStream_t st) { return launch_tau_split(s, 1, nullptr, st); }
 
 int finalize_split(int64_t nq, int k) {
   if (nq <= 0 || nq >= kFinSplitWaves) return 1;
@@ -1619,7 +1655,9 @@ hipError_t launch_finalize_split(const SearchDev& s, int W, uint64_t* part, int3
     pick(IntC<1>{});
   else
     pick(IntC<0>{});
-  if (W > 1 && W * s.k > kMergeWaveMax)
+  if (W > 1 && W * s.k > kMergeWaveMax && s.k <= kMergeHeadsMax && W <= kWave)
+    hipLaunchKernelGGL(k_fin_merge_heads, dim3((unsigned)s.nq), dim3(kMergeThreads), 0, st, s, W, part, pst);
+  else if (W > 1 && W * s.k > kMergeWaveMax)
     hipLaunchKernelGGL(k_fin_merge_block, dim3((unsigned)s.nq), dim3(kMergeThreads), 0, st, s, W, part, pst);
   else if (W > 1)
     hipLaunchKernelGGL(k_fin_merge, dim3((unsigned)((s.nq + kWaves - 1) / kWaves)), dim3(kThreads), 0, st, s, W,

@@ -257,7 +257,7 @@ std::vector<DBuf*> rbq_index::all_buffers() {
           &ws.chunk_qcode,
           &ws.seedk, &ws.q_order, &ws.lstats, &ws.q_boot, &ws.q_rerank, &ws.q_cand, &ws.pair_pt, &ws.q_m, &ws.qn, &ws.nprobe_q, &ws.q_fb, &ws.feats, &ws.tmp,
           &ws.mf_cnt, &ws.mf_pair_off, &ws.mf_unit_off, &ws.mf_pairs, &ws.mf_rows, &ws.mf_units, &ws.units0,
-          &ws.units1, &ws.fin_part, &ws.fin_pst, &ws.tau_part,
+          &ws.units1, &ws.fin_part, &ws.fin_pst,
           &mlp.w32, &mlp.wbf, &mlp.wfrag, &mlp.grad, &mlp.m, &mlp.v, &mlp.act};
 }
 
@@ -705,7 +705,6 @@ rbq_status ensure_workspace(rbq_index* idx, int64_t nq, int nprobe, int k, int c
     HIPCHK(w.fin_part.ensure((size_t)nq * fin_w * k * 8));
     HIPCHK(w.fin_pst.ensure((size_t)nq * fin_w * 2 * 4));
   }
-  if (tau_split(fin_w, k) > 1) HIPCHK(w.tau_part.ensure((size_t)nq * std::min(kMaxK, 4 * k) * 8));
   return RBQ_OK;
 }
 
@@ -937,7 +936,7 @@ rbq_status run_search(rbq_index* idx, const float* queries, int64_t nq, const rb
   HIPCHK(rec(2));
   HIPCHK(launch_scan_popcnt(s, 0, grid0, st));
   HIPCHK(rec(3));
-  HIPCHK(launch_tau_split(s, tau_split(fin_w, o.k), (uint64_t*)idx->ws.tau_part.p, st));
+  HIPCHK(launch_tau(s, st));
   // the batched scan's grouping of pairs by list (timed with the bootstrap
   // rerank, so that the phase-1 events bound the scan kernel alone)
   if (mfma) HIPCHK(launch_group_mfma(s, st));

@@ -118,3 +118,28 @@ def test_block_rerank_equals_wave_rerank(dim, k, metric):
         e = idx.search(q[:8], k, nprobe, rerank_waves=1, scan_kernel=R.RBQ_SCAN_POPCNT, stats=True)
         assert e[2]["candidates"] == idx.search(q[:8], k, nprobe, **kw)[2]["candidates"]
     idx.close()
+
+
+@pytest.mark.parametrize("dim,k", [(20, 1), (64, 16), (255, 64), (300, 65), (600, 25), (1100, 100)])
+def test_bootstrap_and_merge_of_small_batches(dim, k):
+    """Bootstrap reranks by a block (batches below 2048) and by a wave, and merges of
+    the rerank's shares of every form (few keys; heads of up to 64 sorted lists; a
+    sort), against the exact distances of the codes reranked: with a bound that
+    never prunes (eps0 large) every result is the exact top k of the probed lists."""
+    import torch
+    _say(f"bootstrap {dim} {k}")
+    R, idx, data, cent, rng = _index(dim, sizes=[300, 7, 0, 1500, 64, 3, 300, 260, 900, 128])
+    R.rbq_index_set_eps0(idx.h, 200.0)
+    q = (cent[rng.integers(0, len(cent), 2100)] + rng.standard_normal((2100, dim))).astype(np.float32)
+    qc = torch.from_numpy(q).cuda()
+    d64 = ((data[None].astype(np.float64) - q[:12, None].astype(np.float64)) ** 2).sum(-1)
+    want = np.sort(d64, 1)[:, :k]
+    ref = None
+    for nq, waves in ((2100, 1), (2047, 1), (12, 1), (12, 2), (12, 40), (12, 64), (1, 64)):
+        ids, d, _ = idx.search(qc[:nq], k, len(cent), rerank_waves=waves, scan_kernel=R.RBQ_SCAN_POPCNT)
+        ids, d = ids[:12].cpu().numpy(), d[:12].cpu().numpy()
+        ref = ref or (ids, d)
+        assert np.array_equal(ids, ref[0][:nq]) and np.array_equal(d, ref[1][:nq]), (nq, waves)
+    # FP32 sums of dim terms: relative error below (dim / 8 + 8) 2^-23
+    assert (np.abs(ref[1] - want) <= want * (dim / 8 + 8) * 2.0 ** -23 + 1e-12).all()
+    idx.close()
