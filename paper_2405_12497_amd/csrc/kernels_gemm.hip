@@ -14,6 +14,9 @@ namespace rbq {
 //   the 16 columns c of group g: c = 64 (g / 4) + 4 (g % 4) + 16 j + e,
 //   j, e < 4, c < N (ceil(N / 64) * 4 groups per row). A group is the 16
 //   values one lane holds of a row of its wave's 64-column tile.
+// MODE 2: the values of MODE 1, of which only each row's smallest per wave tile
+//   (16 WT columns) is written, as (bits << 32 | column): 8 bytes where the
+//   values are 64 WT, and no pass over them.
 namespace {
 
 // ---------------------------------------------------------------- FP32 MFMA GEMM
@@ -43,6 +46,7 @@ struct GemmJob {
   int N, K;
   const float* bn;
   float* gmin;
+  uint64_t* best;
 };
 
 // LDS of one block: double-buffered A and B tiles, and MODE 1's row norms.
@@ -72,7 +76,7 @@ __device__ __forceinline__ void gemm_tile(const GemmJob& j, int64_t tm, int tn, 
   float* __restrict__ gmin = j.gmin;
   auto& As = L.As;
   auto& Bs = L.Bs;
-  float* an_s = L.an;   // ||A[m]||^2 of the tile's rows (MODE 1)
+  float* an_s = L.an;   // ||A[m]||^2 of the tile's rows (MODE 1, 2)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int64_t m0 = tm * BT;
   const int n0 = tn * BT;
@@ -147,7 +151,7 @@ __device__ __forceinline__ void gemm_tile(const GemmJob& j, int64_t tm, int tn, 
       rb[u] = v;
     }
   };
-  // MODE 1: thread f accumulates the squares of its four columns of row f / 4
+  // MODE 1, 2: thread f accumulates the squares of its four columns of row f / 4
   // as each A tile is stashed; the row's four threads (f % 4) add up at the end
   float asq[NLD];
 #pragma unroll
@@ -158,7 +162,7 @@ __device__ __forceinline__ void gemm_tile(const GemmJob& j, int64_t tm, int tn, 
       const int f = tid + 256 * u;
       *reinterpret_cast<float4*>(&As[buf][f >> 2][(f & 3) * 4]) = ra[u];
       *reinterpret_cast<float4*>(&Bs[buf][f / (BT / 4)][(f % (BT / 4)) * 4]) = rb[u];
-      if (MODE == 1) {
+      if (MODE >= 1) {
         asq[u] = fmaf(ra[u].x, ra[u].x, asq[u]);
         asq[u] = fmaf(ra[u].y, ra[u].y, asq[u]);
         asq[u] = fmaf(ra[u].z, ra[u].z, asq[u]);
@@ -194,7 +198,7 @@ __device__ __forceinline__ void gemm_tile(const GemmJob& j, int64_t tm, int tn, 
     __syncthreads();
     buf ^= 1;
   }
-  if (MODE == 1) {
+  if (MODE >= 1) {
 #pragma unroll
     for (int u = 0; u < NLD; ++u) {
       float v = asq[u];
@@ -205,6 +209,31 @@ __device__ __forceinline__ void gemm_tile(const GemmJob& j, int64_t tm, int tn, 
     __syncthreads();
   }
   // output block (i, j): lane holds row fr, columns 4 fg .. 4 fg + 3
+  if constexpr (MODE == 2) {
+    const int tiles = (N + 16 * WT - 1) / (16 * WT), tile = (n0 + wn) / (16 * WT);
+#pragma unroll
+    for (int i = 0; i < WT; ++i) {
+      const int64_t m = m0 + wm + i * 16 + fr;
+      const float am = an_s[wm + i * 16 + fr];
+      uint64_t key = ~0ull;
+#pragma unroll
+      for (int j = 0; j < WT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int n = n0 + wn + j * 16 + 4 * fg + e;
+          const float o = fmaxf(am + bn[min(n, N - 1)] - 2.f * acc[i][j][e], 0.f) + 0.f;   // no -0
+          const uint64_t k = (uint64_t)__float_as_uint(o) << 32 | (uint32_t)n;
+          key = n < N && k < key ? k : key;
+        }
+#pragma unroll
+      for (int o = 16; o < kWave; o <<= 1) {
+        const uint64_t y = __shfl_xor(key, o, kWave);
+        key = y < key ? y : key;
+      }
+      if (fg == 0 && m < M && tile < tiles) j.best[m * tiles + tile] = key;
+    }
+    return;
+  }
   const bool y_vec = (ldy & 3) == 0 && ((uintptr_t)Y & 15) == 0;
   const bool want_gmin = MODE == 1 && WT == 4 && gmin != nullptr && n0 + wn < N;
   const int G = ((N + 63) >> 6) * 4;
@@ -342,7 +371,7 @@ void launch_f32_mfma(const float* A, int64_t lda, const float* sub, const int32_
                      int64_t ldb, float* Y, int64_t ldy, int64_t M, int N, int K, const float* bn,
                      float* gmin, hipStream_t st) {
   // the 128 tile when it still gives at least 1024 blocks, else the 64 tile
-  const GemmJob j{A, lda, sub, sel, B, ldb, Y, ldy, M, N, K, bn, gmin};
+  const GemmJob j{A, lda, sub, sel, B, ldb, Y, ldy, M, N, K, bn, gmin, nullptr};
   if (M <= 0) return;
   if (MODE == 1 && M <= kCdFewMax && !sel && !gmin) {
     const dim3 grid((unsigned)((N + kWave - 1) / kWave));
@@ -773,6 +802,25 @@ hipError_t launch_centroid_dist(const float* Q, int64_t nq, int dim, const float
   return hipGetLastError();
 }
 
+int centroid_best_tiles(int64_t rows, int nlist) {
+  if (rows <= kCdFewMax) return 0;
+  return gemm_f32_wide_tile(rows, nlist) ? (nlist + 63) / 64 : (nlist + 31) / 32;
+}
+
+hipError_t launch_centroid_best(const float* X, int64_t rows, int dim, const float* Ct, const float* cn, int nlist,
+                                uint64_t* best, hipStream_t st) {
+  if (rows <= kCdFewMax) return hipErrorInvalidValue;   // a kernel of its own, whose sums differ
+  const GemmJob j{X,    (int64_t)dim, nullptr, nullptr, Ct, (int64_t)nlist, nullptr, 0, rows, nlist,
+                  dim,  cn,           nullptr, best};
+  if (gemm_f32_wide_tile(rows, nlist))
+    hipLaunchKernelGGL((k_gemm_f32_mfma<2, 4>), dim3((unsigned)((rows + 127) / 128), (nlist + 127) / 128), dim3(256), 0,
+                       st, j);
+  else
+    hipLaunchKernelGGL((k_gemm_f32_mfma<2, 2>), dim3((unsigned)((rows + 63) / 64), (nlist + 63) / 64), dim3(256), 0, st,
+                       j);
+  return hipGetLastError();
+}
+
 hipError_t launch_rotate_centroid(const float* Q, int64_t nq, int dim, const float* P, int dp, float* qrot,
                                   const float* Ct, const float* cn, int nlist, float* D, float* gmin,
                                   hipStream_t st) {
@@ -782,8 +830,8 @@ hipError_t launch_rotate_centroid(const float* Q, int64_t nq, int dim, const flo
                        nullptr, st);
     return launch_centroid_dist(Q, nq, dim, Ct, cn, nlist, D, gmin, st);
   }
-  const GemmJob rot{Q, (int64_t)dim, nullptr, nullptr, P, (int64_t)dp, qrot, (int64_t)dp, nq, dp, dim, nullptr, nullptr};
-  const GemmJob cd{Q, (int64_t)dim, nullptr, nullptr, Ct, (int64_t)nlist, D, (int64_t)nlist, nq, nlist, dim, cn, gmin};
+  const GemmJob rot{Q, (int64_t)dim, nullptr, nullptr, P, (int64_t)dp, qrot, (int64_t)dp, nq, dp, dim, nullptr, nullptr, nullptr};
+  const GemmJob cd{Q, (int64_t)dim, nullptr, nullptr, Ct, (int64_t)nlist, D, (int64_t)nlist, nq, nlist, dim, cn, gmin, nullptr};
   const int tm = (int)((nq + 127) / 128);
   const int rot_tiles = tm * ((dp + 127) / 128), cd_tiles = tm * ((nlist + 127) / 128);
   hipLaunchKernelGGL(k_gemm_rot_cdist, dim3((unsigned)(rot_tiles + cd_tiles)), dim3(256), 0, st, rot, cd, tm,

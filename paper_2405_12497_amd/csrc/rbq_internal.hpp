@@ -428,6 +428,15 @@ hipError_t launch_debug_pack(const uint8_t* qu, int dp, int W, int npl, int qoff
 // (non-empty lists: sum / (scale cnt); writes cent, its transpose and norms).
 hipError_t launch_absmax(const float* x, int64_t n, uint32_t* out, hipStream_t st);
 hipError_t launch_row_argmin(const float* D, int64_t rows, int nlist, int32_t* lab, hipStream_t st);
+// Nearest list per row without the distance matrix: launch_centroid_best leaves
+// each row's smallest (distance bits << 32 | list) of every column tile in best
+// [rows x tiles], tiles = centroid_best_tiles(rows, nlist), the distances those of
+// launch_centroid_dist; launch_row_best takes the smallest of them. tiles = 0: few
+// rows, which launch_centroid_dist computes with another kernel.
+int centroid_best_tiles(int64_t rows, int nlist);
+hipError_t launch_centroid_best(const float* X, int64_t rows, int dim, const float* Ct, const float* cn, int nlist,
+                                uint64_t* best, hipStream_t st);
+hipError_t launch_row_best(const uint64_t* best, int64_t rows, int tiles, int32_t* lab, hipStream_t st);
 hipError_t launch_fixed_sums(const float* x, const int32_t* lab, int64_t rows, int dim, double scale,
                              unsigned long long* sums, unsigned int* cnt, hipStream_t st);
 hipError_t launch_update_centroids(const unsigned long long* sums, const unsigned int* cnt, int nlist, int dim,

@@ -71,3 +71,37 @@ def test_kmeans_deterministic_and_host_device_equal():
     assert obj < 0.95 * obj0
     with pytest.raises(R.RbqError):
         R.rbq_kmeans(data[:50], 100, iters=1)
+
+
+@pytest.mark.parametrize("n,dim,nlist", [(1, 3, 1), (8, 5, 8), (9, 5, 8), (65, 16, 1), (64, 17, 33), (130, 4, 64),
+                                         (1000, 30, 65), (17000, 12, 1000), (16500, 7, 1024), (70000, 20, 257)])
+def test_assignment_is_exact_on_integers(n, dim, nlist):
+    """Integer data: every FP32 distance is exact, so the assignment is the exact
+    argmin with ties (many, and every centroid twice) to the lower list."""
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    print(f"[assign {n} {dim} {nlist}]", flush=True)
+    rng = np.random.default_rng(n + nlist)
+    data = rng.integers(-6, 7, (n, dim)).astype(np.float32)
+    cent = rng.integers(-6, 7, (nlist, dim)).astype(np.float32)
+    cent[nlist // 2:] = cent[:nlist - nlist // 2]
+    if n < nlist:
+        nlist = n
+        cent = cent[:n]
+    _, got = R.rbq_kmeans(torch.from_numpy(data).cuda(), nlist, iters=0, init=torch.from_numpy(cent).cuda())
+    d = torch.from_numpy(data).double()
+    c = torch.from_numpy(cent).double()
+    dist = (d * d).sum(1)[:, None] + (c * c).sum(1) - 2 * d @ c.T
+    want = (dist == dist.min(1, keepdim=True).values).int().argmax(1)   # the first of equal ones
+    assert np.array_equal(np.asarray(got.cpu() if torch.is_tensor(got) else got), want.numpy())
+
+
+def test_assignment_without_finite_distances():
+    """Rows beyond FP32's range have no finite distance: list 0."""
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    data = np.ones((100, 8), np.float32)
+    data[7] = 3e38
+    _, got = R.rbq_kmeans(torch.from_numpy(data).cuda(), 4, iters=0,
+                          init=torch.from_numpy(np.arange(32, dtype=np.float32).reshape(4, 8)).cuda())
+    assert int(got[7]) == 0
