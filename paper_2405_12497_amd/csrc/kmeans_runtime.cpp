@@ -39,16 +39,22 @@ rbq_status fail(rbq_status st, const char* fmt, ...) {
 // The first `take` entries of a seeded Fisher-Yates shuffle of 0..n-1
 // (SplitMix64 counter stream), in increasing order when `sorted`.
 std::vector<int64_t> seeded_choice(int64_t n, int64_t take, uint64_t seed, bool sorted) {
-  std::vector<int64_t> perm(n);
-  for (int64_t i = 0; i < n; ++i) perm[i] = i;
+  std::vector<int32_t> perm(n);   // n <= INT32_MAX
+  for (int64_t i = 0; i < n; ++i) perm[i] = (int32_t)i;
   for (int64_t i = 0; i < take; ++i) {
     const uint64_t r = host_splitmix64(seed ^ (0x4B4D000000000000ull + (uint64_t)i));
     const int64_t j = i + (int64_t)(r % (uint64_t)(n - i));
     std::swap(perm[i], perm[j]);
   }
-  perm.resize(take);
-  if (sorted) std::sort(perm.begin(), perm.end());
-  return perm;
+  if (!sorted) return std::vector<int64_t>(perm.begin(), perm.begin() + take);
+  // in increasing order from a bitmap (65,536 of 300,000: 0.2 ms, sorted 5 ms)
+  std::vector<uint64_t> bits((size_t)(n + 63) / 64, 0);
+  for (int64_t i = 0; i < take; ++i) bits[perm[i] >> 6] |= 1ull << (perm[i] & 63);
+  std::vector<int64_t> out;
+  out.reserve(take);
+  for (size_t w = 0; w < bits.size(); ++w)
+    for (uint64_t b = bits[w]; b; b &= b - 1) out.push_back((int64_t)w * 64 + __builtin_ctzll(b));
+  return out;
 }
 
 // Nearest centroid of each row of X [rows x dim] (FP32 distances on the matrix

@@ -503,7 +503,7 @@ rbq_status build_impl(rbq_index* idx, const float* data, int64_t n, const std::v
   idx->h_P.swap(P);
   idx->h_cent = cent;
   idx->h_list_off = off;
-  idx->h_ids = ids;
+  idx->h_ids.swap(ids);
   idx->n = n;
   rbq_status rs = upload_model(idx, st);
   if (rs != RBQ_OK) return rs;
@@ -514,7 +514,7 @@ rbq_status build_impl(rbq_index* idx, const float* data, int64_t n, const std::v
   HIPCHK(idx->d_ids.ensure((size_t)n * 8));
   HIPCHK(launch_zero_u32(idx->d_codes.p, (int64_t)npad * W * 2, st));
   HIPCHK(launch_zero_u32(idx->d_fac.p, (int64_t)npad * 2, st));
-  HIPCHK(hipMemcpyAsync(idx->d_ids.p, ids.data(), (size_t)n * 8, hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(idx->d_ids.p, idx->h_ids.data(), (size_t)n * 8, hipMemcpyHostToDevice, st));
   TmpBuf listof;
   HIPCHK(listof.ensure((size_t)n * 4));
   {
@@ -533,7 +533,7 @@ rbq_status build_impl(rbq_index* idx, const float* data, int64_t n, const std::v
     for (int64_t p0 = 0; p0 < n; p0 += blk) {
       const int64_t m = std::min(blk, n - p0);
       for (int64_t r = 0; r < m; ++r)
-        std::memcpy(&stage[(size_t)r * D], data + (size_t)ids[p0 + r] * D, (size_t)D * 4);
+        std::memcpy(&stage[(size_t)r * D], data + (size_t)idx->h_ids[p0 + r] * D, (size_t)D * 4);
       HIPCHK(hipMemcpy((float*)idx->d_raw.p + (size_t)p0 * D, stage.data(), (size_t)m * D * 4,
                        hipMemcpyHostToDevice));
     }
