@@ -959,29 +959,44 @@ rbq_status run_search(rbq_index* idx, const float* queries, int64_t nq, const rb
   return RBQ_OK;
 }
 
-// Scan kernel of an untuned search with scan_kernel = RBQ_SCAN_AUTO: the
-// fragment scan where enough queries share each list, else the popcount scan
-// (identical results). m = pairs per list: a 32 x 32 block of the fragment scan
-// costs the same for 1 or 32 queries, and grouping the pairs about 20 us a
-// search, so the line lies where the popcount scan's cost per code, which grows
-// with the code width, makes up for both. Measured on 200 to 300 codes per list
-// (popcount against fragment scan, us per search): W = 2, m = 16: 444 / 437, m =
-// 8: 289 / 318; W = 4, m = 32: 276 / 265, m = 16: 205 / 220; W = 5, m = 8: 258 /
-// 249, m = 4: 204 / 220; W = 8, m = 6: 283 / 271, m = 4: 243 / 248; W = 12, m =
-// 3: 429 / 379, m = 1: 280 / 299; W = 15, m = 4: 346 / 323, m = 2: 284 / 290.
-// Batches with little to scan (pairs x codes per list x words) don't earn the
-// grouping back, whatever m is. 64 lists of 1,562 codes, W = 12: 19 M words 227 /
-// 245, 77 M 374 / 319; W = 2: 13 M 164 / 198, 51 M 287 / 284; 256 lists of 781
-// codes, W = 7: 22 M 261 / 245; 512 lists of 39 codes, W = 5: 13 M 273 / 276 and
-// 230 / 216, 51 M 566 / 457. Lists shorter than a block's 32 codes leave it
-// mostly empty.
+// Scan kernel of an untuned search with scan_kernel = RBQ_SCAN_AUTO: the MFMA
+// scan where enough queries share each list, else the popcount scan (identical
+// results). m = pairs per list: a block of the MFMA scan costs the same for 1 or 32
+// queries, and grouping the pairs 20 to 40 us a search, so the line lies where the
+// popcount scan's cost per code, which grows with the code width and B_q, makes up
+// for both: in m, and in the batch's work (pairs x codes per list x words). Lists
+// shorter than a block's 32 codes leave it mostly empty. Measured on 200 to 300
+// codes per list unless noted (popcount / MFMA, us per search):
+//   B_q <= 4, W <= 16 (FP6 x FP4 fragments): W = 2, m = 16: 444 / 437, m = 8: 289 /
+//   318; W = 4, m = 32: 276 / 265, m = 16: 205 / 220; W = 5, m = 8: 258 / 249, m =
+//   4: 204 / 220; W = 8, m = 6: 283 / 271, m = 4: 243 / 248; W = 12, m = 3: 429 /
+//   379, m = 1: 280 / 299; W = 15, m = 4: 346 / 323, m = 2: 284 / 290. In 64 lists of
+//   1,562 codes, W = 12: 19 M words 227 / 245, 77 M 374 / 319; W = 2: 13 M 164 /
+//   198, 51 M 287 / 284; 256 lists of 781 codes, W = 7: 22 M 261 / 245.
+//   B_q <= 4, W > 16 (block form): W = 18, m = 16, 29 M: 546 / 561, m = 32, 58 M:
+//   1229 / 1217, m = 64: 1020 / 850; W = 64, m = 16, 31 M: 837 / 907, m = 32, 61 M:
+//   786 / 767.
+//   B_q > 4 (block form, int8): W = 1, 51 M: 779 / 830; W = 2, m = 16, 31 M: 430 /
+//   450, m = 32, 64 M: 625 / 600; W = 4, m = 16, 19 M: 323 / 343, m = 32, 38 M: 509 /
+//   483; W = 5, 16 M: 416 / 426, 32 M: 459 / 335; W = 7, m = 4: 264 / 277, m = 16, 22
+//   M: 419 / 373; W = 12, m = 2, 10 M: 295 / 307, 24 M: 469 / 423, m = 8: 673 / 560;
+//   W = 15, m = 47: 3058 / 953; W = 18, 14 M: 721 / 731, 29 M: 748 / 601.
 int auto_scan_kernel(const rbq_index* idx, int64_t nq, double nprobe) {
-  if (!scan_frag_available(idx->W, idx->prm.bq <= 4 ? 4 : 8)) return RBQ_SCAN_POPCNT;
   const int W = idx->W;
   const double pairs = (double)nq * nprobe, m = pairs / idx->nlist;
-  const double line = W <= 1 ? 48 : W <= 4 ? 24 : W <= 7 ? 8 : W <= 11 ? 6 : 4;
   const double codes = (double)idx->n / idx->nlist;
-  const double work = pairs * codes * W, least = W <= 4 ? 48e6 : 20e6;
+  const double work = pairs * codes * W;
+  double line, least;
+  if (idx->prm.bq > 4) {
+    line = W <= 4 ? 24 : W <= 7 ? 12 : W <= 11 ? 6 : 2;
+    least = W <= 1 ? 128e6 : W <= 3 ? 64e6 : W <= 4 ? 38e6 : W <= 7 ? 20e6 : 16e6;
+  } else if (scan_frag_available(W, 4)) {
+    line = W <= 1 ? 48 : W <= 4 ? 24 : W <= 7 ? 8 : W <= 11 ? 6 : 4;
+    least = W <= 4 ? 48e6 : 20e6;
+  } else {
+    line = 32;
+    least = 60e6;
+  }
   return m >= line && codes >= 32 && work >= least ? RBQ_SCAN_MFMA : RBQ_SCAN_POPCNT;
 }
 

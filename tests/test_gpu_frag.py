@@ -67,14 +67,15 @@ def test_search_equals_popcount(words, nq, metric):
     idx.close()
 
 
-def test_automatic_choice_equals_popcount():
+@pytest.mark.parametrize("dim,bq", [(700, 4), (700, 8), (1100, 4)])
+def test_automatic_choice_equals_popcount(dim, bq):
     """Shapes on both sides of the automatic choice's line, host and device buffers."""
     import torch
-    _say("automatic choice")
+    _say(f"automatic choice {dim} {bq}")
     rng = np.random.default_rng(3)
-    R, idx, data, cent, _ = _index(700, sizes=[70] * 1200)
-    for nq in (20, 400, 700):
-        q = (cent[rng.integers(0, len(cent), nq)] + rng.standard_normal((nq, 700))).astype(np.float32)
+    R, idx, data, cent, _ = _index(dim, sizes=[70] * (1200 if bq == 4 and dim < 1000 else 300), bq=bq)
+    for nq in (20, 400, 700, 1300):
+        q = (cent[rng.integers(0, len(cent), nq)] + rng.standard_normal((nq, dim))).astype(np.float32)
         a = idx.search(torch.from_numpy(q).cuda(), 10, 24, scan_kernel=R.RBQ_SCAN_POPCNT, stats=True)
         b = idx.search(torch.from_numpy(q).cuda(), 10, 24, stats=True)
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and a[2] == b[2]
@@ -85,7 +86,7 @@ def test_automatic_choice_equals_popcount():
         # a replay pads the batch, so an eager search of the same rows is the reference
         assert torch.equal(g[0], a[0]) and torch.equal(g[1], a[1])
     # queries that are not finite: no candidate of theirs survives, in either scan
-    q = rng.standard_normal((400, 700)).astype(np.float32)
+    q = rng.standard_normal((400, dim)).astype(np.float32)
     q[3, 5] = np.nan
     q[7, 1] = np.inf
     q[9] = 1e30
