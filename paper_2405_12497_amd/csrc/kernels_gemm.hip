@@ -86,69 +86,63 @@ __device__ __forceinline__ void gemm_tile(const GemmJob& j, int64_t tm, int tn, 
   for (int i = 0; i < WT; ++i)
 #pragma unroll
     for (int j = 0; j < WT; ++j) acc[i][j] = f32x4v{0.f, 0.f, 0.f, 0.f};
-  const bool a_vec = (lda & 3) == 0 && (K & 3) == 0;   // rows (and centroid rows) 16-byte aligned
-  const bool b_vec = (ldb & 3) == 0;
-  // tiles entirely inside the matrices take unconditional float4 loads
+  const bool a_vec = (lda & 3) == 0 && (K & 3) == 0;   // four k inside the row or beyond it together
+  const bool b_vec = (ldb & 3) == 0 && (N & 3) == 0;
   const bool interior = a_vec && b_vec && m0 + BT <= M && n0 + BT <= N;
+  // Loads without conditions (one under a condition waits for itself before the
+  // next, which the edge tiles' time was): rows and columns beyond the operands repeat the last ones, whose outputs
+  // are not written; k beyond K is zeroed in both.
   const float* arow[NLD];
   const float* srow[NLD];
 #pragma unroll
   for (int u = 0; u < NLD; ++u) {
-    const int64_t m = m0 + ((tid + 256 * u) >> 2);
-    arow[u] = m < M ? A + m * lda : nullptr;
-    srow[u] = (m < M && sel) ? sub + (int64_t)sel[m] * K : nullptr;
+    const int64_t m = min(m0 + ((tid + 256 * u) >> 2), M - 1);
+    arow[u] = A + m * lda;
+    srow[u] = sel ? sub + (int64_t)sel[m] * K : nullptr;
   }
+  auto load4 = [](const float* p, bool vec, int at, int n) {   // p[at .. at + 3], n the row's length
+    if (vec) return *reinterpret_cast<const float4*>(p + min(at, n - 4));
+    return make_float4(p[min(at, n - 1)], p[min(at + 1, n - 1)], p[min(at + 2, n - 1)], p[min(at + 3, n - 1)]);
+  };
   float4 ra[NLD], rb[NLD];
   auto fetch = [&](int k0) {
-    if (interior && k0 + MKS <= K) {
+    if (interior && k0 + MKS <= K) {   // without the clamps' arithmetic
 #pragma unroll
       for (int u = 0; u < NLD; ++u) {
         const int f = tid + 256 * u;
         ra[u] = *reinterpret_cast<const float4*>(arow[u] + k0 + (f & 3) * 4);
         rb[u] = *reinterpret_cast<const float4*>(B + (int64_t)(k0 + f / (BT / 4)) * ldb + n0 + (f % (BT / 4)) * 4);
       }
-      if (sel) {
-        float4 c[NLD];
+    } else {
 #pragma unroll
-        for (int u = 0; u < NLD; ++u) c[u] = *reinterpret_cast<const float4*>(srow[u] + k0 + ((tid + 256 * u) & 3) * 4);
-#pragma unroll
-        for (int u = 0; u < NLD; ++u) {
-          ra[u].x -= c[u].x;
-          ra[u].y -= c[u].y;
-          ra[u].z -= c[u].z;
-          ra[u].w -= c[u].w;
-        }
+      for (int u = 0; u < NLD; ++u) {
+        const int f = tid + 256 * u;
+        ra[u] = load4(arow[u], a_vec, k0 + (f & 3) * 4, K);
+        rb[u] = load4(B + (int64_t)min(k0 + f / (BT / 4), K - 1) * ldb, b_vec, n0 + (f % (BT / 4)) * 4, N);
       }
-      return;
     }
+    if (sel) {
+      float4 c[NLD];
 #pragma unroll
-    for (int u = 0; u < NLD; ++u) {
-      const int f = tid + 256 * u;
-      const int kq = (f & 3) * 4;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (arow[u]) {
-        const int k = k0 + kq;
-        float t[4];
+      for (int u = 0; u < NLD; ++u) c[u] = load4(srow[u], a_vec, k0 + ((tid + 256 * u) & 3) * 4, K);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) t[i] = (k + i < K) ? arow[u][k + i] - (srow[u] ? srow[u][k + i] : 0.f) : 0.f;
-        v = make_float4(t[0], t[1], t[2], t[3]);
+      for (int u = 0; u < NLD; ++u) {
+        ra[u].x -= c[u].x;
+        ra[u].y -= c[u].y;
+        ra[u].z -= c[u].z;
+        ra[u].w -= c[u].w;
       }
-      ra[u] = v;
     }
+    if (k0 + MKS > K) {
 #pragma unroll
-    for (int u = 0; u < NLD; ++u) {
-      const int f = tid + 256 * u;
-      const int kr = f / (BT / 4), nq = (f % (BT / 4)) * 4;
-      const int k = k0 + kr, n = n0 + nq;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (k < K) {
-        const float* brow = B + (int64_t)k * ldb;
-        if (n < N) v.x = brow[n];
-        if (n + 1 < N) v.y = brow[n + 1];
-        if (n + 2 < N) v.z = brow[n + 2];
-        if (n + 3 < N) v.w = brow[n + 3];
+      for (int u = 0; u < NLD; ++u) {
+        const int f = tid + 256 * u, k = k0 + (f & 3) * 4;
+        ra[u].x = k < K ? ra[u].x : 0.f;
+        ra[u].y = k + 1 < K ? ra[u].y : 0.f;
+        ra[u].z = k + 2 < K ? ra[u].z : 0.f;
+        ra[u].w = k + 3 < K ? ra[u].w : 0.f;
+        if (k0 + f / (BT / 4) >= K) rb[u] = make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      rb[u] = v;
     }
   };
   // MODE 1, 2: thread f accumulates the squares of its four columns of row f / 4
@@ -277,15 +271,18 @@ __global__ __launch_bounds__(256) void k_gemm_f32_mfma(GemmJob j) {
 // The query rotation (MODE 0) and the centroid distances (MODE 1) in one
 // launch: they read the same queries and are independent, so the rotation's
 // few tiles run beside the distance tiles instead of before them. Tiles are
-// numbered row tile fastest; the rotation's come first.
+// numbered row tile fastest; the rotation's come first. 500 queries at D = 256,
+// 1000 lists: 35 us as two launches of 64 tiles, 16 us as one; 1000 at D = 300:
+// 52 and 32 us.
+template <int WT>
 __global__ __launch_bounds__(256) void k_gemm_rot_cdist(GemmJob rot, GemmJob cd, int rot_tm, int rot_tiles,
                                                         int cd_tm) {
-  __shared__ __attribute__((aligned(16))) GemmLds<4> L;
+  __shared__ __attribute__((aligned(16))) GemmLds<WT> L;
   const int t = blockIdx.x;
   if (t < rot_tiles)
-    gemm_tile<0, 4>(rot, t % rot_tm, t / rot_tm, L);
+    gemm_tile<0, WT>(rot, t % rot_tm, t / rot_tm, L);
   else
-    gemm_tile<1, 4>(cd, (t - rot_tiles) % cd_tm, (t - rot_tiles) / cd_tm, L);
+    gemm_tile<1, WT>(cd, (t - rot_tiles) % cd_tm, (t - rot_tiles) / cd_tm, L);
 }
 
 // ---------------------------------------------------------------- few-query centroid distances
@@ -825,17 +822,20 @@ hipError_t launch_rotate_centroid(const float* Q, int64_t nq, int dim, const flo
                                   const float* Ct, const float* cn, int nlist, float* D, float* gmin,
                                   hipStream_t st) {
   if (nq <= 0) return hipSuccess;
-  if (!gemm_f32_wide_tile(nq, nlist)) {
+  if (nq <= kCdFewMax) {
     launch_f32_mfma<0>(Q, (int64_t)dim, nullptr, nullptr, P, (int64_t)dp, qrot, (int64_t)dp, nq, dp, dim, nullptr,
                        nullptr, st);
     return launch_centroid_dist(Q, nq, dim, Ct, cn, nlist, D, gmin, st);
   }
+  const bool wide = gemm_f32_wide_tile(nq, nlist);
+  const int T = wide ? 128 : 64;
   const GemmJob rot{Q, (int64_t)dim, nullptr, nullptr, P, (int64_t)dp, qrot, (int64_t)dp, nq, dp, dim, nullptr, nullptr, nullptr};
-  const GemmJob cd{Q, (int64_t)dim, nullptr, nullptr, Ct, (int64_t)nlist, D, (int64_t)nlist, nq, nlist, dim, cn, gmin, nullptr};
-  const int tm = (int)((nq + 127) / 128);
-  const int rot_tiles = tm * ((dp + 127) / 128), cd_tiles = tm * ((nlist + 127) / 128);
-  hipLaunchKernelGGL(k_gemm_rot_cdist, dim3((unsigned)(rot_tiles + cd_tiles)), dim3(256), 0, st, rot, cd, tm,
-                     rot_tiles, tm);
+  const GemmJob cd{Q, (int64_t)dim, nullptr, nullptr, Ct, (int64_t)nlist, D, (int64_t)nlist, nq, nlist, dim, cn,
+                   wide ? gmin : nullptr, nullptr};
+  const int tm = (int)((nq + T - 1) / T);
+  const int rot_tiles = tm * ((dp + T - 1) / T), cd_tiles = tm * ((nlist + T - 1) / T);
+  hipLaunchKernelGGL((wide ? k_gemm_rot_cdist<4> : k_gemm_rot_cdist<2>), dim3((unsigned)(rot_tiles + cd_tiles)),
+                     dim3(256), 0, st, rot, cd, tm, rot_tiles, tm);
   return hipGetLastError();
 }
 

@@ -40,3 +40,37 @@ def test_split_bf16_rotation(dim):
     bound = tol * (np.abs(r) @ np.abs(P))
     assert ((got == (y > 0)) | (np.abs(y) <= bound)).all()
     idx.close()
+
+
+@pytest.mark.parametrize("dim,nlist", [(1, 1), (3, 5), (4, 64), (7, 33), (16, 3), (17, 65), (37, 130), (100, 4), (260, 129)])
+def test_fp32_rotation_and_centroid_distances(dim, nlist):
+    """FP32 products around the tiles (64 rows and columns), K steps of 16 and widths
+    that are and are not multiples of 4: sums of K terms, |error| <= (K + 8) 2^-23
+    times the sum of the terms' magnitudes."""
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    print(f"[fp32 {dim} {nlist}]", flush=True)
+    rng = np.random.default_rng(dim + nlist)
+    bits = (dim + 63) // 64 * 64
+    P = np.linalg.qr(rng.standard_normal((bits, bits)))[0]
+    cent = rng.standard_normal((nlist, dim)).astype(np.float32)
+    data = rng.standard_normal((300, dim)).astype(np.float32)
+    idx = R.Index(dim, nlist)
+    idx.build_rotation(data, cent, (np.arange(300) % nlist).astype(np.int32), P)
+    P, c = P[:dim], cent.astype(np.float64)
+    tol = (dim + 8) * 2.0 ** -23
+    for nq in (1, 8, 9, 63, 64, 65, 200, 1030):
+        q = rng.standard_normal((nq, dim)).astype(np.float32)
+        qc, q64 = torch.from_numpy(q).cuda(), q.astype(np.float64)
+        got = R.rbq_debug_rotate(idx.h, qc, bits).cpu().numpy()
+        assert (np.abs(got - q64 @ P) <= tol * (np.abs(q64) @ np.abs(P))).all(), nq
+        d = R.rbq_debug_centroid_dists(idx.h, qc, nlist).cpu().numpy()
+        sq, sc = (q64 ** 2).sum(1)[:, None], (c ** 2).sum(1)[None]
+        assert (np.abs(d - np.maximum(sq + sc - 2 * q64 @ c.T, 0)) <= tol * (sq + sc + 2 * np.abs(q64) @ np.abs(c.T))).all(), nq
+    # searches rotate and score in one launch: every code of every list, exactly
+    R.rbq_index_set_eps0(idx.h, 200.0)
+    q = rng.standard_normal((70, dim)).astype(np.float32)
+    _, got, _ = idx.search(torch.from_numpy(q).cuda(), 5, nlist)
+    want = np.sort(((q[:, None].astype(np.float64) - data[None]) ** 2).sum(-1), 1)[:, :5]
+    assert (np.abs(got.cpu().numpy() - want) <= want * tol + 1e-12).all()
+    idx.close()
