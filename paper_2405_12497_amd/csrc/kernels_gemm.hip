@@ -271,8 +271,8 @@ __global__ __launch_bounds__(256) void k_gemm_f32_mfma(GemmJob j) {
 // The query rotation (MODE 0) and the centroid distances (MODE 1) in one
 // launch: they read the same queries and are independent, so the rotation's
 // few tiles run beside the distance tiles instead of before them. Tiles are
-// numbered row tile fastest; the rotation's come first. 500 queries at D = 256,
-// 1000 lists: 35 us as two launches of 64 tiles, 16 us as one; 1000 at D = 300:
+// numbered row tile fastest; the rotation's come first. 500 queries at D = 200,
+// 1024 lists: 35 us as two launches of 64 tiles, 16 us as one; 1000 at D = 300, 2048:
 // 52 and 32 us.
 template <int WT>
 __global__ __launch_bounds__(256) void k_gemm_rot_cdist(GemmJob rot, GemmJob cd, int rot_tm, int rot_tiles,

@@ -336,9 +336,7 @@ __global__ __launch_bounds__(kThreads) void k_prep_q(SearchDev s) {
 // One wave per query: chunk and code prefixes over its probed pairs (64 ranks
 // per step, shuffle scans), and the bootstrap: whole chunks in probe order up
 // to the first chunk at which the covered codes reach s.boot.
-__global__ __launch_bounds__(kThreads) void k_plan(SearchDev s) {
-  const int64_t q = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
-  if (q >= s.nq) return;   // whole waves
+__device__ __forceinline__ void plan_body(const SearchDev& s, int64_t q) {
   const int lane = lane_id();
   int P = s.nprobe;
   if (s.nprobe_q) P = uniform_i32(min(max(s.nprobe_q[q], 1), s.nprobe));
@@ -392,6 +390,11 @@ __global__ __launch_bounds__(kThreads) void k_plan(SearchDev s) {
     s.q_n0[q] = n0;
     s.q_ncode[q] = code;
   }
+}
+
+__global__ __launch_bounds__(kThreads) void k_plan(SearchDev s) {
+  const int64_t q = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
+  if (q < s.nq) plan_body(s, q);   // whole waves
 }
 
 // k_plan for a wide probe (nprobe > kPlanWaveMax), one block per query:
@@ -526,7 +529,9 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan_block(SearchDev s) {
 // over blocks of kOffQ queries (thread t: queries 4t..4t+3 of the block):
 // k_offsets_sum writes each block's five sums; k_offsets_scan adds the sums
 // of the blocks before it and scans its own queries (shuffle scan in each
-// wave, then the four wave totals).
+// wave, then the four wave totals). A batch of one block needs no sums, and up
+// to kWaves queries are planned by that block as well: such searches are chains
+// of launches of 3 to 5 us each.
 constexpr int kOffThreads = kOffQ / 4;
 
 __device__ __forceinline__ void off_counts(const SearchDev& s, int64_t q, int64_t (&v)[5]) {
@@ -554,10 +559,6 @@ __device__ __forceinline__ int64_t wave_incl_scan_i64(int64_t x) {
 __global__ __launch_bounds__(kOffThreads) void k_offsets_sum(SearchDev s) {
   __shared__ int64_t wtot[kOffThreads / kWave][5];
   const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
-  if (blockIdx.x == 0 && t == 0) {
-    s.counters[0] = 0;
-    s.counters[1] = 0;
-  }
   const int64_t q0 = (int64_t)blockIdx.x * kOffQ + (int64_t)t * 4;
   int64_t sum[5] = {0, 0, 0, 0, 0};
 #pragma unroll
@@ -582,11 +583,15 @@ __global__ __launch_bounds__(kOffThreads) void k_offsets_sum(SearchDev s) {
   }
 }
 
-__global__ __launch_bounds__(kOffThreads) void k_offsets_scan(SearchDev s) {
+__device__ __forceinline__ void offsets_scan_body(const SearchDev& s) {
   __shared__ int64_t wtot[kOffThreads / kWave][5];
   __shared__ int64_t carry[5];
   const int t = threadIdx.x, lane = lane_id(), wave = t >> 6;
   constexpr int kNW = kOffThreads / kWave;
+  if (blockIdx.x == 0 && t == 0) {
+    s.counters[0] = 0;
+    s.counters[1] = 0;
+  }
   // carry: the sums of the blocks before this one
   {
     int64_t c[5] = {0, 0, 0, 0, 0};
@@ -643,6 +648,16 @@ __global__ __launch_bounds__(kOffThreads) void k_offsets_scan(SearchDev s) {
     }
     if (blockIdx.x == gridDim.x - 1 && t == 0) outs[a][s.nq] = total;
   }
+}
+
+__global__ __launch_bounds__(kOffThreads) void k_offsets_scan(SearchDev s) { offsets_scan_body(s); }
+
+static_assert(kOffThreads == kThreads, "one block plans and scans");
+__global__ __launch_bounds__(kThreads) void k_plan_offsets(SearchDev s) {   // at most kWaves queries
+  const int wave = uniform_i32(threadIdx.x >> 6);
+  if (wave < s.nq) plan_body(s, wave);
+  __syncthreads();
+  offsets_scan_body(s);
 }
 
 // A lane per probe rank: the descriptors of its chunks,
@@ -1541,12 +1556,15 @@ hipError_t launch_plan(const SearchDev& s, hipStream_t st) {
     }
     const size_t shm = 2 * ((size_t)plan_pad(s.nprobe) + 1) * sizeof(int32_t);
     hipLaunchKernelGGL(k_plan_block, dim3((unsigned)s.nq), dim3(kPlanThreads), shm, st, s);
+  } else if (s.nq <= kWaves) {
+    hipLaunchKernelGGL(k_plan_offsets, dim3(1), dim3(kThreads), 0, st, s);
+    return hipGetLastError();
   } else {
     const dim3 gq((unsigned)((s.nq + kWaves - 1) / kWaves));
     hipLaunchKernelGGL(k_plan, gq, dim3(kThreads), 0, st, s);
   }
   const dim3 gb((unsigned)((s.nq + kOffQ - 1) / kOffQ));
-  hipLaunchKernelGGL(k_offsets_sum, gb, dim3(kOffThreads), 0, st, s);
+  if (gb.x > 1) hipLaunchKernelGGL(k_offsets_sum, gb, dim3(kOffThreads), 0, st, s);
   hipLaunchKernelGGL(k_offsets_scan, gb, dim3(kOffThreads), 0, st, s);
   return hipGetLastError();
 }

@@ -144,3 +144,22 @@ def test_bootstrap_and_merge_of_small_batches(dim, k):
     # FP32 sums of dim terms: relative error below (dim / 8 + 8) 2^-23
     assert (np.abs(ref[1] - want) <= want * (dim / 8 + 8) * 2.0 ** -23 + 1e-12).all()
     idx.close()
+
+
+@pytest.mark.parametrize("nprobe", [1, 7, 10])
+def test_batches_around_the_plan(nprobe):
+    """Batches planned by one launch (4 queries), scanned by one block (1024) and by
+    several: a query's results and the counts do not depend on the batch."""
+    import torch
+    _say(f"plan {nprobe}")
+    R, idx, data, cent, rng = _index(40, sizes=[300, 7, 0, 1500, 64, 3, 300, 260, 900, 128])
+    q = torch.from_numpy((cent[rng.integers(0, len(cent), 2050)] +
+                          rng.standard_normal((2050, 40))).astype(np.float32)).cuda()
+    kw = dict(rerank_waves=1, scan_kernel=R.RBQ_SCAN_POPCNT)
+    ref = idx.search(q, 10, nprobe, **kw)
+    for nq in (1, 3, 4, 5, 64, 1023, 1024, 1025, 2048, 2049):
+        a = idx.search(q[:nq], 10, nprobe, stats=True, **kw)
+        assert torch.equal(a[0], ref[0][:nq]) and torch.equal(a[1], ref[1][:nq]), nq
+        b = idx.search(q[:nq], 10, nprobe, rerank_waves=1, scan_kernel=R.RBQ_SCAN_MFMA, stats=True)
+        assert torch.equal(a[0], b[0]) and a[2] == b[2], nq
+    idx.close()
