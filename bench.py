@@ -29,15 +29,14 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
-INT8_PEAK_TOPS = 5000.0        # MI355X dense int8 MFMA
-FP8_PEAK_TFLOPS = 5000.0       # MI355X dense FP8 MFMA (the FP8 x FP4 products run at the FP8 operand's rate)
+FP6_PEAK_TFLOPS = 10000.0      # MI355X dense FP6 / FP4 MFMA (FP6 queries x FP4 codes)
 
 # Kernel sources per scan kind; stored counter readings apply only while their
 # sources hash to the value they were taken on.
 SCAN_SOURCES = {
     "popcnt": ("paper_2405_12497_amd/csrc/kernels_popcnt.hip", "paper_2405_12497_amd/csrc/scan_code.hpp",
                "paper_2405_12497_amd/csrc/rbq_internal.hpp"),
-    "mfma": ("paper_2405_12497_amd/csrc/kernels_mfma.hip", "paper_2405_12497_amd/csrc/scan_code.hpp",
+    "mfma": ("paper_2405_12497_amd/csrc/kernels_frag.hip", "paper_2405_12497_amd/csrc/scan_code.hpp",
              "paper_2405_12497_amd/csrc/rbq_internal.hpp"),
     "finalize": ("paper_2405_12497_amd/csrc/kernels_scan.hip", "paper_2405_12497_amd/csrc/wave_select.hpp",
                  "paper_2405_12497_amd/csrc/rbq_internal.hpp"),
@@ -111,11 +110,10 @@ def scan_roofline(kernel, codes, ms, dim, bpc, wkey):
     if kernel in ("mfma", "mfma_fp4"):
         ops = codes * 2.0 * dim
         achieved = ops / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
-        peak = INT8_PEAK_TOPS if kernel == "mfma" else FP8_PEAK_TFLOPS
-        name = ("k_scan_mfma_w<false,12,1> (phase-1 batched scan, int8 MFMA)" if kernel == "mfma" else
-                "k_scan_mfma_w<true,12,1> (phase-1 batched scan, FP8 x FP4 MFMA)")
+        peak = FP6_PEAK_TFLOPS
+        name = "k_scan_frag<12> (phase-1 batched scan, FP6 x FP4 MFMA)"
         return {"bound": "mfma", "achieved": achieved, "peak": peak,
-                "unit": "TOP/s" if kernel == "mfma" else "TFLOP/s", "frac": achieved / peak,
+                "unit": "TFLOP/s", "frac": achieved / peak,
                 "traffic": stored_traffic("learned_" + kernel, wkey), "sq_counters": stored_sq("learned_" + kernel, wkey),
                 "kernel": name,
                 "algorithmic_ops_per_code": 2 * dim, "ops_per_launch": ops, "avg_launch_ms": ms,
@@ -362,7 +360,7 @@ def bench_embed(args):
 
 def bench_gist(args):
     """GIST-like 1M x 960 (Zipf list sizes), 4096 lists, 10,000 queries in
-    batches of 256, top-100, BF16x3 rotation: the batched int8-MFMA scan vs
+    batches of 256, top-100, BF16x3 rotation: the batched MFMA scan vs
     the popcount scan at the nprobe reaching recall@100 >= 0.95, and the
     rotation's error against an FP64 rotation by the same P."""
     import torch
@@ -455,7 +453,7 @@ def bench_gist(args):
         "n_gpus": 1, "steps": len(batches), "warmup": len(batches),
         "ms_per_step": res[best]["ms_per_batch"],
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "int1xint4->int32 scan (int8 MFMA or popcount), fp32 estimator/rerank", "data": "synthetic",
+        "dtype": "int1xint4->int32 scan (FP6 x FP4 MFMA, exact, or popcount), fp32 estimator/rerank", "data": "synthetic",
         "config": {
             "workload": f"batched scan: {n} GIST-like vectors D={dim} (values in [0,1], decaying spectrum, "
                         f"Zipf(1.1) components), {nlist} lists, BF16x3 rotation, {nq} queries in batches of "
@@ -468,7 +466,7 @@ def bench_gist(args):
         },
         "roofline": {"bound": "hbm", "achieved": res["mfma"]["phase1_scan_gb_per_s"], "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": res["mfma"]["phase1_scan_gb_per_s"] / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "k_scan_mfma (phase-1 scan, batches of 256)", "algorithmic_bytes_per_code": bpc,
+                     "kernel": "k_scan_frag<15> (phase-1 scan, batches of 256)", "algorithmic_bytes_per_code": bpc,
                      "avg_launch_ms": res["mfma"]["phase1_scan_ms_per_batch"]},
         "cpu_baseline": None,
     }

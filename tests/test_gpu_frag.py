@@ -163,3 +163,54 @@ def test_batches_around_the_plan(nprobe):
         b = idx.search(q[:nq], 10, nprobe, rerank_waves=1, scan_kernel=R.RBQ_SCAN_MFMA, stats=True)
         assert torch.equal(a[0], b[0]) and a[2] == b[2], nq
     idx.close()
+
+
+@pytest.mark.parametrize("words", range(5, 17))
+def test_wide_pair_quantisation(words):
+    """4-bit rounding of 5 to 16 words against its definition, floor((r - min) / step
+    + u) with the counter stream's u: equal wherever that argument is at least 1e-3
+    from an integer (FP32 steps of 15 levels are good to 1e-5), one level off at most
+    elsewhere. Seeds with and without carries that differ inside a draw; batches of
+    few pairs and of several pairs per wave; empty and NaN residuals."""
+    import torch
+    from oracle import rabitq_oracle as O
+    from paper_2405_12497_amd import rabitq as R
+    _say(f"pair quantisation {words}")
+    dim, dp, nlist = 64 * words - 9, 64 * words, 40
+    for seed in (7, 960):
+        rng = np.random.default_rng(words)
+        P = np.linalg.qr(rng.standard_normal((dp, dp)))[0]
+        cent = rng.standard_normal((nlist, dim)).astype(np.float32)
+        data = rng.standard_normal((200, dim)).astype(np.float32)
+        idx = R.Index(dim, nlist, seed=seed)
+        idx.build_rotation(data, cent, (np.arange(200) % nlist).astype(np.int32), P)
+        crot = (cent.astype(np.float64) @ P[:dim]).astype(np.float32)
+        for nq, nprobe, base in ((3, 5, 0), (2600, 33, 1000)):
+            q = rng.standard_normal((nq, dim)).astype(np.float32)
+            q[1] = cent[3]                 # a residual of rounding errors only
+            q[2, 5] = np.nan
+            lists = np.stack([rng.permutation(nlist)[:nprobe] for _ in range(nq)]).astype(np.int32)
+            qc = torch.from_numpy(q).cuda()
+            qu, scal = R.rbq_debug_quantize(idx.h, qc, torch.from_numpy(lists).cuda(), dp, qid_base=base)
+            qu, scal = qu.cpu().numpy().reshape(nq, nprobe, dp), scal.cpu().numpy().reshape(nq, nprobe, 4)
+            rot = R.rbq_debug_rotate(idx.h, qc, dp).cpu().numpy()
+            assert (qu[2] == 0).all()      # NaN quantises to 0
+            near = total = 0
+            for qi in [0] + list(range(3, nq, 97)):
+                for r in range(0, nprobe, 1 if nq < 10 else 4):
+                    lid = int(lists[qi, r])
+                    res = (rot[qi] - crot[lid]).astype(np.float64)
+                    step = (res.max() - res.min()) / 15
+                    v = (res - res.min()) / step + O.rounding_uniforms_fast(seed, base + qi, lid, dp)
+                    clear = np.abs(v - np.rint(v)) > 1e-3
+                    want = np.clip(np.floor(v), 0, 15)
+                    assert (qu[qi, r][clear] == want[clear]).all(), (seed, qi, r)
+                    assert (np.abs(qu[qi, r] - want) <= 1).all()
+                    b = np.linalg.norm(res)     # v_l and the step are of the unit residual
+                    assert abs(scal[qi, r, 1] * b - res.min()) <= 1e-5 * np.abs(res).max()
+                    assert abs(scal[qi, r, 2] * b - step) <= 1e-5 * step
+                    assert scal[qi, r, 3] == qu[qi, r].sum()
+                    near += int((~clear).sum())
+                    total += dp
+            assert near <= 0.01 * total
+        idx.close()
