@@ -50,13 +50,13 @@ SCAN_SOURCES = {
 COUNTERS = {
     "learned_mfma": {
         "kind": "mfma",
-        "sources_sha256": "effe3d43f3f1890aee0b9d23aa294e21b38897b58d613440da5cbb9991cac9e9",
+        "sources_sha256": "ad4072d5573d860684a1921e5c99bdd714838d9181abc11606f4ad7c422a65b8",
         "workload": "learned n=10000000 nlist=16384 batch=10000",
-        "fetch_kib": 2308801.4, "write_kib": 1008186.1, "fetch_scale": 2.0, "write_scale": 1.0,
+        "fetch_kib": 4963236.9, "write_kib": 1396291.4, "fetch_scale": 2.0, "write_scale": 1.0,
         # SQ counters of the same dispatches: SQ_VALU_MFMA_BUSY_CYCLES and
         # 4 x SQ_INSTS_VALU over (GRBM_GUI_ACTIVE / 8 XCDs) x 1024 SIMDs, and
         # SQ_WAIT_INST_ANY / SQ_WAVE_CYCLES
-        "sq": {"mfma_busy": 0.186, "valu_busy": 0.640, "wave_wait_frac": 0.451},
+        "sq": {"mfma_busy": 0.231, "valu_busy": 0.666, "wave_wait_frac": 0.468},
     },
     "fullscan": {
         "kind": "popcnt",
@@ -66,9 +66,9 @@ COUNTERS = {
     },
     "finalize": {
         "kind": "finalize",
-        "sources_sha256": "f4437b650ca24495580c991eacba6fa405e43ffd54af47d10710ab9f9d3d2c62",
+        "sources_sha256": "f535122d88c91b26cfddb8661a9129d93ea762c6628f4ca5fa23871ae3578623",
         "workload": "learned n=10000000 nlist=16384 batch=10000",
-        "fetch_kib": 6355367.4, "write_kib": 2191.3, "fetch_scale": 2.0, "write_scale": 1.0,
+        "fetch_kib": 6354790.0, "write_kib": 2193.6, "fetch_scale": 2.0, "write_scale": 1.0,
     },
 }
 NPROBE_SWEEP = (8, 12, 16, 20, 24, 28, 32, 40, 48, 64, 80, 96, 128, 160, 192, 256)
