@@ -60,9 +60,9 @@ COUNTERS = {
     },
     "fullscan": {
         "kind": "popcnt",
-        "sources_sha256": "1278f4a38262bec68207cdf10beb63ee30fda320a5b4b5e8326dab9947da0949",
+        "sources_sha256": "3a0063d6bf2330625c01267babf525523e5c419d2e16e5553123b03000d58a62",
         "workload": "fullscan n=10000000 nlist=16384",
-        "fetch_kib": 540390.8, "write_kib": 624.3, "fetch_scale": 2.0, "write_scale": 1.0,
+        "fetch_kib": 540338.8, "write_kib": 645.5, "fetch_scale": 2.0, "write_scale": 1.0,
     },
     "finalize": {
         "kind": "finalize",
