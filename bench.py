@@ -50,7 +50,7 @@ SCAN_SOURCES = {
 COUNTERS = {
     "learned_mfma": {
         "kind": "mfma",
-        "sources_sha256": "ad4072d5573d860684a1921e5c99bdd714838d9181abc11606f4ad7c422a65b8",
+        "sources_sha256": "32a79657e099ed37ed1fc915ed1f1e3365b8f386c8536182c91e2d89f3f2f6d3",
         "workload": "learned n=10000000 nlist=16384 batch=10000",
         "fetch_kib": 4963236.9, "write_kib": 1396291.4, "fetch_scale": 2.0, "write_scale": 1.0,
         # SQ counters of the same dispatches: SQ_VALU_MFMA_BUSY_CYCLES and
