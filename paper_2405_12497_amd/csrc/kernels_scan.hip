@@ -1590,16 +1590,20 @@ int finalize_split(int64_t nq, int k) {
 
 namespace {
 // Waves that rerank together for each of a query's W shares (the order of its
-// rounds, and so the results, is the same): one where the shares fill the chip
-// evenly, kFinBlockWaves where a share of one or two lists makes the longest much
-// longer than the mean, or there are too few shares. 256 queries at D = 960, k =
-// 100, 8 lists over W = 8: 950 us / 590 us (mean of a share 100 us, longest 950);
-// 64 shares: 21 / 18 us at D = 768, 12.1 / 10.5 us at D = 128; even shares: 500
-// queries at D = 128, 40 lists over W = 4: 27 / 39 us, 1000 at D = 300, 48 over 2:
-// 163 / 172 us.
+// rounds, and so the results, is the same). Blocks of kFinBlockWaves shorten a
+// share's chain of rounds but fit a third as many shares on the chip at once, so
+// they take over where there are few shares, or where shares of one or two lists
+// (the longest much longer than the mean) have much to fetch: k results of D
+// columns, k D >= 8000. Searches of 100 to 1000 queries by one wave / by blocks:
+// D = 128, k = 10: 92 to 119 / 102 to 136 us; D = 300, k = 10: 139 to 173 / 154 to
+// 190; D = 768, k = 10: 183 to 379 / 194 to 376; D = 960, k = 10: 342 to 1073 / 292 to
+// 764; D = 128, k = 100: 276 to 492 / 242 to 421; D = 960, k = 100: 781 to 2220 / 568
+// to 1727. 64 shares: D = 768 21 / 18 us, D = 128 12.1 / 10.5 us of rerank. Even
+// shares: 500 queries at D = 200, 40 lists over W = 4: 27 / 39 us, 1000 at D = 300,
+// 48 over 2: 163 / 172 us.
 constexpr int kFinBlockWaves = 4;
-int finalize_waves(int64_t units, int W, int nprobe) {
-  return W > 1 && (units <= 512 || nprobe <= 2 * W) ? kFinBlockWaves : 1;
+int finalize_waves(int64_t units, int W, int nprobe, int k, int dim) {
+  return W > 1 && (units <= 512 || (nprobe <= 2 * W && (int64_t)k * dim >= 8000)) ? kFinBlockWaves : 1;
 }
 constexpr int kOrderBins = 64;
 
@@ -1654,7 +1658,7 @@ hipError_t launch_query_order(const int32_t* nprobe_q, int64_t nq, int nprobe, i
 hipError_t launch_finalize_split(const SearchDev& s, int W, uint64_t* part, int32_t* pst, hipStream_t st) {
   if (s.nq <= 0) return hipSuccess;
   if (W < 1 || (W > 1 && (!part || !pst || W * s.k > kFinMergeCap))) return hipErrorInvalidValue;
-  const int cw = finalize_waves(s.nq * W, W, s.nprobe);
+  const int cw = finalize_waves(s.nq * W, W, s.nprobe, s.k, s.dim);
   const size_t shm = (size_t)(cw == 1 ? kWaves : 1) * (kFinWin + kFinRoundMax + s.k + (s.k & 1)) * sizeof(uint64_t) +
                      (cw == 1 ? 0 : (size_t)s.dim * sizeof(float));
   const dim3 grid((unsigned)(cw == 1 ? (s.nq * W + kWaves - 1) / kWaves : s.nq * W));
