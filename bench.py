@@ -66,7 +66,7 @@ COUNTERS = {
     },
     "finalize": {
         "kind": "finalize",
-        "sources_sha256": "7d50d4342bac1e8f6b7eaa1fe28c083601f3f0a5d22ad855bc0c616f57605362",
+        "sources_sha256": "f2b2613a1d2dbd6f0b87d67802c662479030287239b53d7c09bb62ba25c00642",
         "workload": "learned n=10000000 nlist=16384 batch=10000",
         "fetch_kib": 6354790.0, "write_kib": 2193.6, "fetch_scale": 2.0, "write_scale": 1.0,
     },

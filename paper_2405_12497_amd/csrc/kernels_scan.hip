@@ -872,9 +872,10 @@ __device__ __forceinline__ uint32_t sortable_bits(float x) {
 // distances, twice the columns in flight. A single wave's round trips bound small
 // batches: 256 queries at D = 960, k = 100, 134 us before (eight waves per query,
 // each selecting, and a merge kernel) and 80 us now; 333 at D = 768, k = 10, 27.6
-// and 21.7 us. From kTauBlock queries on, single waves fill the chip and HBM bounds
-// both (10,000 at D = 768: 1.2 GB in 273 us).
-constexpr int64_t kTauBlock = 2048;
+// and 21.7 us. Above kTauBlock queries single waves fill the chip
+// (a search of 1100 at D = 128: 147 us either way, of 2000: 204 us by waves, 210 by
+// blocks) and HBM bounds wide rows (10,000 at D = 768: 1.2 GB in 273 us).
+constexpr int64_t kTauBlock = 1024;
 template <bool WIDE, bool BLOCK>
 __global__ __launch_bounds__(kThreads) void k_tau(SearchDev s) {
   using DS = DistShape<WIDE>;
@@ -1572,7 +1573,7 @@ hipError_t launch_plan(const SearchDev& s, hipStream_t st) {
 
 hipError_t launch_tau(const SearchDev& s, hipStream_t st) {
   if (s.nq <= 0) return hipSuccess;
-  const bool block = s.nq < kTauBlock;
+  const bool block = s.nq <= kTauBlock;
   const dim3 grid((unsigned)(block ? s.nq : (s.nq + kWaves - 1) / kWaves));
   auto kern = dist_wide(s.dim) ? (block ? k_tau<true, true> : k_tau<true, false>)
                                : (block ? k_tau<false, true> : k_tau<false, false>);

@@ -123,7 +123,7 @@ def test_block_rerank_equals_wave_rerank(dim, k, metric):
 
 @pytest.mark.parametrize("dim,k", [(20, 1), (64, 16), (255, 64), (300, 65), (600, 25), (1100, 100)])
 def test_bootstrap_and_merge_of_small_batches(dim, k):
-    """Bootstrap reranks by a block (batches below 2048) and by a wave, and merges of
+    """Bootstrap reranks by a block (batches up to 1024) and by a wave, and merges of
     the rerank's shares of every form (few keys; heads of up to 64 sorted lists; a
     sort), against the exact distances of the codes reranked: with a bound that
     never prunes (eps0 large) every result is the exact top k of the probed lists."""
@@ -136,7 +136,7 @@ def test_bootstrap_and_merge_of_small_batches(dim, k):
     d64 = ((data[None].astype(np.float64) - q[:12, None].astype(np.float64)) ** 2).sum(-1)
     want = np.sort(d64, 1)[:, :k]
     ref = None
-    for nq, waves in ((2100, 1), (2047, 1), (12, 1), (12, 2), (12, 40), (12, 64), (1, 64)):
+    for nq, waves in ((2100, 1), (2047, 1), (1025, 1), (1024, 1), (12, 1), (12, 2), (12, 40), (12, 64), (1, 64)):
         ids, d, _ = idx.search(qc[:nq], k, len(cent), rerank_waves=waves, scan_kernel=R.RBQ_SCAN_POPCNT)
         ids, d = ids[:12].cpu().numpy(), d[:12].cpu().numpy()
         ref = ref or (ids, d)
