@@ -66,7 +66,7 @@ COUNTERS = {
     },
     "finalize": {
         "kind": "finalize",
-        "sources_sha256": "f2b2613a1d2dbd6f0b87d67802c662479030287239b53d7c09bb62ba25c00642",
+        "sources_sha256": "cdc0b918baf37113ef709a0a622302798cd7228b3767081802088d686ffb8fca",
         "workload": "learned n=10000000 nlist=16384 batch=10000",
         "fetch_kib": 6354790.0, "write_kib": 2193.6, "fetch_scale": 2.0, "write_scale": 1.0,
     },

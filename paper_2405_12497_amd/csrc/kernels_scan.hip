@@ -730,8 +730,8 @@ __global__ __launch_bounds__(kThreads) void k_prep_units(SearchDev s, int64_t nu
 // U columns per lane are loaded per round trip, for all NC vectors together
 // (columns past the row read its last one and add 0), so a pass costs
 // ceil(D / (32 U)) round trips; the order of the additions does not depend on
-// U. Every exact distance on the device comes from this routine, so equal
-// vectors get equal bits.
+// U. QL: the query lies in LDS and is read as it is used. Every exact distance
+// on the device comes from this routine, so equal vectors get equal bits.
 constexpr int kLpc = 8;
 
 // One column's contribution: (a - b)^2 for squared L2, a b for the inner

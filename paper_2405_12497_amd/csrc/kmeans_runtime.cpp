@@ -60,25 +60,28 @@ std::vector<int64_t> seeded_choice(int64_t n, int64_t take, uint64_t seed, bool 
 // Nearest centroid of each row of X [rows x dim] (FP32 distances on the matrix
 // cores, ties to the lower list), without their matrix: 65,536 x 1024 at D = 128
 // took 186 us for the distances and 86 us for the minima through memory, 187 and
-// 5 us with the minima taken in the product, and allocating 1 GiB up to 36 ms. Chunks of the rows whose matrix would
-// be 1 GiB keep the grid and the workspace small; a chunk of few rows has distances
-// of another kernel and goes through the matrix.
+// 5 us with the minima taken in the product, and allocating the matrix (in chunks
+// of 1 GiB) up to 36 ms. A chunk of few rows has distances of another kernel and
+// still goes through the matrix; the others run in parts of kBestRows rows, whose
+// workspace stays small.
+constexpr int64_t kBestRows = 65536;
 rbq_status assign_rows(const float* X, int64_t rows, int dim, int nlist, const float* centT, const float* cnorm,
                        DBuf& D, int32_t* lab, hipStream_t st) {
   const int64_t chunk = std::max<int64_t>(1, std::min<int64_t>(rows, (1ll << 30) / ((int64_t)nlist * 4)));
-  auto tiles_of = [&](int64_t m) { return centroid_best_tiles(m, nlist); };
-  int64_t need = 0;
-  for (int64_t m : {chunk, rows % chunk})
-    if (m > 0) need = std::max(need, tiles_of(m) > 0 ? m * tiles_of(m) * 8 : m * (int64_t)nlist * 4);
-  HIPCHK(D.ensure((size_t)need));
   for (int64_t r0 = 0; r0 < rows; r0 += chunk) {
     const int64_t m = std::min(chunk, rows - r0);
-    if (const int tiles = tiles_of(m)) {
-      HIPCHK(launch_centroid_best(X + r0 * dim, m, dim, centT, cnorm, nlist, (uint64_t*)D.p, st));
-      HIPCHK(launch_row_best((const uint64_t*)D.p, m, tiles, lab + r0, st));
-    } else {
+    if (centroid_best_tiles(m, nlist) == 0) {
+      HIPCHK(D.ensure((size_t)m * nlist * 4));
       HIPCHK(launch_centroid_dist(X + r0 * dim, m, dim, centT, cnorm, nlist, (float*)D.p, nullptr, st));
       HIPCHK(launch_row_argmin((const float*)D.p, m, nlist, lab + r0, st));
+      continue;
+    }
+    const int64_t parts = (m + kBestRows - 1) / kBestRows, per = (m + parts - 1) / parts;   // equal parts: none of few rows
+    HIPCHK(D.ensure((size_t)per * ((nlist + 31) / 32) * 8));
+    for (int64_t p0 = 0; p0 < m; p0 += per) {
+      const int64_t r = r0 + p0, n = std::min(per, m - p0);
+      HIPCHK(launch_centroid_best(X + r * dim, n, dim, centT, cnorm, nlist, (uint64_t*)D.p, st));
+      HIPCHK(launch_row_best((const uint64_t*)D.p, n, centroid_best_tiles(n, nlist), lab + r, st));
     }
   }
   return RBQ_OK;

@@ -543,7 +543,8 @@ rbq_status build_impl(rbq_index* idx, const float* data, int64_t n, const std::v
   // rotate residuals and encode, in blocks of rows
   {
     const int dp = idx->dp;
-    const int64_t blk = std::max<int64_t>(64, std::min<int64_t>(n, (int64_t)(256ll << 20) / ((int64_t)dp * 4)));
+    // 64 MiB: enough rows for full launches; allocating takes up to 36 us a MiB
+    const int64_t blk = std::max<int64_t>(64, std::min<int64_t>(n, (int64_t)(64ll << 20) / ((int64_t)dp * 4)));
     TmpBuf y;
     HIPCHK(y.ensure((size_t)blk * dp * 4));
     for (int64_t p0 = 0; p0 < n; p0 += blk) {
