@@ -798,8 +798,8 @@ def bench_learned(args):
         "unit": "queries/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": t_l * 1e3, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": {"mfma": "int8 MFMA scan (1-bit codes x 4-bit queries -> int32)",
-                  "mfma_fp4": "fp8 x fp4 MFMA scan (exact integers)",
+        "dtype": {"mfma": "FP6 x FP4 MFMA scan (1-bit codes x 4-bit queries, exact integers)",
+                  "mfma_fp4": "FP6 x FP4 MFMA scan (1-bit codes x 4-bit queries, exact integers)",
                   "popcnt": "int1 x int4 popcount scan -> int32",
                   "auto": "autotuned scan"}[args.kernel] + ", bf16 MLP, fp32 estimator/rerank",
         "data": "synthetic",

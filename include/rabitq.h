@@ -68,9 +68,9 @@ enum {
   RBQ_SCAN_MFMA = 2,     /* MFMA over queries grouped by list: FP6 (query) x FP4 (code
                             bit) blocks, exact, for B_q <= 4 and codes up to 1024
                             bits, int8 otherwise */
-  RBQ_SCAN_MFMA_FP4 = 3  /* the same contraction on the scaled FP8 (query, E4M3) x
-                            FP4 (code bit, E2M1) MFMA with FP32 accumulation, exact
-                            for B_q <= 4 (RBQ_EUNSUPPORTED above) */
+  RBQ_SCAN_MFMA_FP4 = 3  /* as RBQ_SCAN_MFMA, with FP8 (query, E4M3) x FP4 (code bit,
+                            E2M1) for codes above 1024 bits; exact for B_q <= 4
+                            (RBQ_EUNSUPPORTED above) */
 };
 
 /* What a search ranks by. The codes are the same for every metric.
