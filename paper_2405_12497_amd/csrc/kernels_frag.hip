@@ -85,10 +85,13 @@ struct WaveLds {
 };
 
 // What a lane holds of its query (column): the estimator's constants, the
-// threshold tau - pt (-inf where the column is not scanned: no bound passes),
-// and where its candidates go.
+// threshold tau - pt, where its candidates go, and the outputs that may become
+// candidates: all 16, or none where the column is not scanned (past the unit's
+// pairs, or a chunk the bootstrap has scanned). Its segment then belongs to
+// another column or to the bootstrap, so no value of a bound may let it store.
 struct Column {
   float a1, a2, a0, coefh, pt, thr;
+  uint32_t live;   // 0xFFFF or 0
   Cand* seg;
 };
 
@@ -177,13 +180,14 @@ __device__ __forceinline__ int frag_unit(const SearchDev& s, int64_t start, int 
     wave_lds_sync();
     const int left = n - rb;   // codes of the block that exist, if below 32
     // bounds without the pair term (as est_y / est_dl on the integer product);
-    // fails: bit 15 - i is the sign of thr - bound of output i (two cheap
-    // instructions without a lane mask between them). A NaN bound may count as
-    // passing: the rerank drops it. The factors are read two outputs ahead:
+    // pass: bit 15 - i is the test of output i (an ordered compare, so that a NaN
+    // bound or threshold fails as in the other scans; the sign of thr - bound, which
+    // a NaN may pass, is 1% faster: 1087 to 1105 us of 10,000 queries x 128 lists at
+    // D = 768, compared 1106 to 1136). The factors are read two outputs ahead:
     // left alone, the compiler reads each right before its use to save registers
     // and waits 16 times.
     float low[16];
-    uint32_t fails = 0;
+    uint32_t pass = 0;
     float4 fc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) fc[0][i] = L.fac[4 * grp + i];
@@ -210,11 +214,11 @@ __device__ __forceinline__ int frag_unit(const SearchDev& s, int64_t start, int 
           dbg_lb[o] = low[i] + c.pt;
         }
       } else {
-        fails = __builtin_amdgcn_alignbit(fails, __float_as_uint(c.thr - low[i]), 31);
+        pass = pass + pass + (low[i] <= c.thr ? 1u : 0u);
       }
     }
     if constexpr (!DEBUG) {
-      uint32_t mask = ~fails & 0xFFFFu;   // bit 15 - i: output i passes
+      uint32_t mask = pass & c.live;   // bit 15 - i: output i is a candidate
       if (left < 32) {   // the last block: codes past the end
         const uint32_t v = ~(0xFFFFFFFFu >> left) << (4 * grp);   // this lane's codes: its nibbles from bit 31 down
         mask &= ((v >> 16) & 0xF000u) | ((v >> 12) & 0x0F00u) | ((v >> 8) & 0x00F0u) | ((v >> 4) & 0x000Fu);
@@ -354,9 +358,9 @@ __global__ __launch_bounds__(kThreads, WS <= 6 ? 4 : WS <= 12 && WS != 11 ? 3 : 
       c.a0 = row.a0;
       c.coefh = row.coefh;
       c.pt = row.pt;
-      c.thr = row.thr == row.thr ? row.thr : -__builtin_inff();
+      c.thr = row.thr;
+      c.live = live ? 0xFFFFu : 0u;
       c.seg = s.seg + row.seg + (int64_t)ch * s.chunk;
-      if (!live) c.thr = -__builtin_inff();
       const int count = frag_unit<false, WS>(s, start, n, c, fq, L, [&]() {
         if (ahead) nu = sl.take(s, sl.own + uniform_i32((int)ticket));
       }, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0);
@@ -394,6 +398,7 @@ __global__ __launch_bounds__(kWave) void k_debug_frag(SearchDev s, const PairRec
   c.coefh = t.coefh;
   c.pt = t.pt;
   c.thr = -__builtin_inff();
+  c.live = 0u;
   c.seg = nullptr;
   (void)frag_unit<true, WS>(s, start, (int)(end - start), c, fq, L, NoHook{}, recp, ip, pc, est, dist, lb, lbeg);
 }

@@ -96,6 +96,41 @@ def test_automatic_choice_equals_popcount(dim, bq):
     idx.close()
 
 
+@pytest.mark.parametrize("words", [1, 3, 12, 16])
+def test_nonfinite_base_vectors_equal_popcount(words):
+    """Rows whose factors are NaN or overflow, in lists that units share with one, 31
+    and 33 queries (columns without a pair repeat the last one's) and whose first
+    chunk some queries scan in the bootstrap: such a row is a candidate where its
+    bound compares as one and disturbs no other, so ids, distances and counts are the
+    popcount scan's."""
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    _say(f"non-finite rows {words}")
+    dim, per, counts = 64 * words - 5, 1100, (1, 31, 33, 64, 2, 5)   # two chunks per list
+    rng = np.random.default_rng(words)
+    cent = rng.standard_normal((len(counts), dim)).astype(np.float32) * 2
+    assign = np.repeat(np.arange(len(counts)), per).astype(np.int32)
+    data = (cent[assign] + rng.standard_normal((len(assign), dim))).astype(np.float32)
+    bad = [np.nan, np.copysign(np.nan, -1.0), np.inf, -np.inf, 1e30, -1e30, 3e38, 1e19]
+    for lst in range(len(counts)):
+        for i, v in enumerate(bad):   # among the first chunk's codes and the second's
+            data[lst * per + 37 * i + lst] = v
+            data[lst * per + 1030 + 7 * i + lst, i % dim] = v
+    idx = R.Index(dim, len(counts), seed=words)
+    idx.build(torch.from_numpy(data).cuda(), cent, assign)
+    near = np.repeat(np.arange(len(counts)), counts)
+    q = torch.from_numpy((cent[near] + rng.standard_normal((len(near), dim))).astype(np.float32)).cuda()
+    many = q.repeat(16, 1)   # enough pairs for the automatic choice of wide codes
+    for k, nprobe in ((10, 1), (1, 2), (100, 3), (10, 6)):
+        for x, kerns in ((q, (R.RBQ_SCAN_MFMA, R.RBQ_SCAN_MFMA_FP4)), (many, (R.RBQ_SCAN_AUTO, R.RBQ_SCAN_MFMA))):
+            a = idx.search(x, k, nprobe, scan_kernel=R.RBQ_SCAN_POPCNT, stats=True)
+            assert torch.isfinite(a[1]).all()   # healthy rows enough for every query
+            for kern in kerns:
+                b = idx.search(x, k, nprobe, scan_kernel=kern, stats=True)
+                assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1]) and a[2] == b[2], (k, nprobe, kern)
+    idx.close()
+
+
 @pytest.mark.parametrize("dim,k,metric", [(30, 1, 0), (128, 100, 0), (255, 10, 1), (260, 33, 0), (771, 10, 2), (1027, 64, 0)])
 def test_block_rerank_equals_wave_rerank(dim, k, metric):
     """A query's rerank shares by one wave each (a large batch of many lists) and
