@@ -1023,12 +1023,13 @@ __device__ __forceinline__ int fin_lds_words(int k) { return kFinWin + kFinRound
 // where one share is much longer than the rest. With CW > 1 a block of CW waves
 // takes one share: wave 0 gathers, chooses the rounds and merges as a single wave
 // would, all waves compute a round's distances, with the query in LDS and 2 to 4
-// times the fetches in flight.
+// times the fetches in flight (at a multiple of 16 bytes: 256
+// queries at D = 960, k = 100 take 555 us, 655 with its float4 reads 8 bytes off).
 template <bool WIDE, int CW>
 __global__ __launch_bounds__(CW == 1 ? kThreads : CW * kWave, CW == 1 && !WIDE ? 4 : 3) void k_finalize(
     SearchDev s, int W, uint64_t* __restrict__ part, int32_t* __restrict__ pst) {
   using DS = DistShape<WIDE>;
-  extern __shared__ uint64_t fin_lds[];
+  extern __shared__ __attribute__((aligned(16))) uint64_t fin_lds[];   // the query in it is read as float4
   __shared__ int32_t round_n;   // CW > 1: entries of the round, -1 when there is none left
   const int wave = uniform_i32(threadIdx.x >> 6), lane = lane_id();
   if (s.prof_acc && blockIdx.x == 0 && threadIdx.x == 0) {   // codes estimated by each scan phase
@@ -1595,13 +1596,13 @@ namespace {
 // share's chain of rounds but fit a third as many shares on the chip at once, so
 // they take over where there are few shares, or where shares of one or two lists
 // (the longest much longer than the mean) have much to fetch: k results of D
-// columns, k D >= 8000. Searches of 100 to 1000 queries by one wave / by blocks:
-// D = 128, k = 10: 92 to 119 / 102 to 136 us; D = 300, k = 10: 139 to 173 / 154 to
-// 190; D = 768, k = 10: 183 to 379 / 194 to 376; D = 960, k = 10: 342 to 1073 / 292 to
-// 764; D = 128, k = 100: 276 to 492 / 242 to 421; D = 960, k = 100: 781 to 2220 / 568
-// to 1727. 64 shares: D = 768 21 / 18 us, D = 128 12.1 / 10.5 us of rerank. Even
-// shares: 500 queries at D = 200, 40 lists over W = 4: 27 / 39 us, 1000 at D = 300,
-// 48 over 2: 163 / 172 us.
+// columns, k D >= 8000. Reranks of 100, 250 and 500 queries over 8 lists of about 146
+// codes by one wave / by blocks, us: D = 128, k = 10: 24, 23, 24 / 28, 35, 36; D = 300,
+// k = 10: 31, 34, 38 / 35, 48, 52; D = 768, k = 10: 37, 40, 50 / 39, 50, 62; D = 960 (uneven
+// lists), k = 10: 139, 207, 415 / 80, 129, 215; k = 100: 378, 528, 906 / 218, 361, 578; D =
+// 128, k = 100: 82, 50, 54 / 80, 56, 60. 512 shares or less: D = 768 24 / 18 us, D = 128
+// 17.7 / 16.5, D = 960 57 / 34. Even shares: 500 queries at D = 200, 40 lists over
+// W = 4: 30 / 43 us, 1000 at D = 300, 48 over 2: 160 / 157 us.
 constexpr int kFinBlockWaves = 4;
 int finalize_waves(int64_t units, int W, int nprobe, int k, int dim) {
   return W > 1 && (units <= 512 || (nprobe <= 2 * W && (int64_t)k * dim >= 8000)) ? kFinBlockWaves : 1;
