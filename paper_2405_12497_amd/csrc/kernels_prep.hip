@@ -218,18 +218,19 @@ __global__ __launch_bounds__(kThreads) void k_prep_wide(SearchDev s, int kPairs)
 
 template <int W>
 void launch_w(const SearchDev& s, dim3 grid, int per, bool mix, hipStream_t st) {
-  if (s.frag) {
+  auto run = [&](auto fmt) {
+    constexpr int FMT = decltype(fmt)::value;
     if (mix)
-      hipLaunchKernelGGL((k_prep_wide<W, kFragments, true>), grid, dim3(kThreads), 0, st, s, per);
+      hipLaunchKernelGGL((k_prep_wide<W, FMT, true>), grid, dim3(kThreads), 0, st, s, per);
     else
-      hipLaunchKernelGGL((k_prep_wide<W, kFragments, false>), grid, dim3(kThreads), 0, st, s, per);
-  } else if (s.qu8) {
-    hipLaunchKernelGGL((k_prep_wide<W, kPlain, true>), grid, dim3(kThreads), 0, st, s, per);
-  } else if (mix) {
-    hipLaunchKernelGGL((k_prep_wide<W, kPlanesOnly, true>), grid, dim3(kThreads), 0, st, s, per);
-  } else {
-    hipLaunchKernelGGL((k_prep_wide<W, kPlanesOnly, false>), grid, dim3(kThreads), 0, st, s, per);
-  }
+      hipLaunchKernelGGL((k_prep_wide<W, FMT, false>), grid, dim3(kThreads), 0, st, s, per);
+  };
+  if (s.frag)
+    run(IntC<kFragments>{});
+  else if (s.qu8)
+    run(IntC<kPlain>{});
+  else
+    run(IntC<kPlanesOnly>{});
 }
 
 }  // namespace

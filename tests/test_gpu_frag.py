@@ -249,3 +249,53 @@ def test_wide_pair_quantisation(words):
                     total += dp
             assert near <= 0.01 * total
         idx.close()
+
+
+@pytest.mark.parametrize("words,seed", [(5, 7), (8, 960), (12, 7), (12, 960), (16, 7), (15, 960)])
+def test_search_quantises_as_the_export(words, seed):
+    """What a search writes of a pair (bit planes; the fragment scan's rows) holds the
+    exported rounding: one list of two chunks and a part, the first the bootstrap's.
+    The candidates counted are that chunk's codes and the later ones whose exported
+    bound is at most the k-th exact distance of the 4k best exported estimates. FP32
+    sums and the export's FP32 scalars: codes within 1e-5 of the distances' scale of
+    that threshold may count either way."""
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    _say(f"search rounding {words} {seed}")
+    dim, n, k, nq, base = 64 * words - 9, 2500, 10, 24, 50
+    rng = np.random.default_rng(words)
+    cent = rng.standard_normal((1, dim)).astype(np.float32)
+    data = (cent + rng.standard_normal((n, dim))).astype(np.float32)
+    q = (cent + rng.standard_normal((nq, dim))).astype(np.float32)
+    idx = R.Index(dim, 1, seed=seed)
+    idx.build(data, cent, np.zeros(n, np.int32))
+    qc = torch.from_numpy(q).cuda()
+    order = R.rbq_debug_list_ids(idx.h, 0, n)
+    one = torch.zeros((nq, 1), dtype=torch.int32, device="cuda")
+
+    def bounds(first_id):
+        """Fewest and most candidates of each query, rounded as ids first_id, ... are."""
+        qu, scal = R.rbq_debug_quantize(idx.h, qc, one, 64 * words, qid_base=first_id)
+        scal = scal.cpu().numpy()
+        lo, hi = [], []
+        for i in range(nq):
+            _, _, _, dist, lb = R.rbq_debug_scan(idx.h, 0, qu[i], *map(float, scal[i, :3]), n)
+            dist, lb = dist.cpu().numpy()[:1024], lb.cpu().numpy().astype(np.float64)
+            d = ((data[order].astype(np.float64) - q[i]) ** 2).sum(1)
+            best = np.argsort(dist, kind="stable")
+            eps = 1e-5 * d.mean()
+            taus = [np.sort(d[best[:m]])[k - 1] for m in (4 * k - 1, 4 * k, 4 * k + 1)]   # equal estimates at the cut
+            lo.append(1024 + int((lb[1024:] <= min(taus) - eps).sum()))
+            hi.append(1024 + int((lb[1024:] <= max(taus) + eps).sum()))
+        return np.array(lo), np.array(hi)
+
+    lo, hi = bounds(base)
+    share = (lo - 1024) / (n - 1024)
+    assert 0.02 < share.mean() < 0.8 and (hi - lo).mean() < 10
+    other = bounds(base + 1000)[0]   # another rounding of the same queries: the counts tell them apart
+    assert (np.abs(other - lo) > hi - lo).mean() > 0.5
+    for kern in (R.RBQ_SCAN_POPCNT, R.RBQ_SCAN_MFMA):
+        got = np.array([idx.search(qc[i:i + 1], k, 1, qid_base=base + i, scan_kernel=kern, rerank_waves=1,
+                                   stats=True)[2]["candidates"] for i in range(nq)])
+        assert ((lo <= got) & (got <= hi)).all(), (kern, lo, got, hi)
+    idx.close()
