@@ -1517,29 +1517,33 @@ hipError_t launch_prep(const SearchDev& s, bool units, hipStream_t st) {
     if (units) hipLaunchKernelGGL(k_units, dim3((unsigned)ublocks), dim3(kThreads), 0, st, s);
     return hipGetLastError();
   }
-  // the rest (B_q > 4 or more than 16 words): one pair per wave, two up to W = 8
+  // the rest: one pair per wave, two up to W = 8. Codes of up to 16 words come here
+  // with B_q > 4 only; 4000 queries x 40 lists at B_q = 8 take 192 us with the exact
+  // width at W = 12 and 208 us with the 16-word bound; at W = 15 it makes no
+  // difference (230 us).
   const bool p4 = s.npl == 4;
-#define RBQ_PREP(WS_, PPW_)                                                                          \
-  do {                                                                                              \
-    if (p4)                                                                                         \
-      hipLaunchKernelGGL((k_prep_reg<WS_, PPW_, 4>), grid(PPW_), dim3(kThreads), 0, st, s);         \
-    else                                                                                            \
-      hipLaunchKernelGGL((k_prep_reg<WS_, PPW_, 0>), grid(PPW_), dim3(kThreads), 0, st, s);         \
-  } while (0)
+#define RBQ_PREP(WS_, PPW_, NPL_) \
+  hipLaunchKernelGGL((k_prep_reg<WS_, PPW_, NPL_>), grid(PPW_), dim3(kThreads), 0, st, s)
   switch (s.W) {
     case 1: launch_prep_q<1>(s, ublocks, qblocks, st); return hipGetLastError();
     case 2: launch_prep_q<2>(s, ublocks, qblocks, st); return hipGetLastError();
     case 3: launch_prep_q<3>(s, ublocks, qblocks, st); return hipGetLastError();
     case 4: launch_prep_q<4>(s, ublocks, qblocks, st); return hipGetLastError();
+    case 12: RBQ_PREP(12, 1, 0); break;
     default:
       if (s.W <= 8) {
-        RBQ_PREP(8, 2);
+        RBQ_PREP(8, 2, 0);
       } else if (s.W <= 16) {
-        RBQ_PREP(16, 1);
+        RBQ_PREP(16, 1, 0);
       } else if (s.W <= 32) {
-        RBQ_PREP(32, 1);
+        if (p4)
+          RBQ_PREP(32, 1, 4);
+        else
+          RBQ_PREP(32, 1, 0);
+      } else if (p4) {
+        RBQ_PREP(64, 1, 4);
       } else {
-        RBQ_PREP(64, 1);
+        RBQ_PREP(64, 1, 0);
       }
   }
 #undef RBQ_PREP

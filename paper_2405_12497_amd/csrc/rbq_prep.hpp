@@ -79,12 +79,14 @@ __device__ __forceinline__ void pair_ip_term(const SearchDev& s, int64_t g, int6
   if (lane_id() == 0) s.pair_pt[g] = s.q_m[q] - gdot;
 }
 
-// Randomised rounding of residual v: floor((v - rmin) scale + u), at most qmax,
-// with u = f 2^-24, as a float. The sum is never negative, so truncation is the
-// floor. One rounding of the product for words 2 j, one of the product and sum
-// together for words 2 j + 1: fixed here so that every kernel gives the same
-// quantised query. A pair that is not live has scale 0, so it quantises to 0,
-// as does a NaN (the median with a NaN is the smaller of the other two).
+// k_prep_wide's randomised rounding of residual v: floor((v - rmin) scale + u), at
+// most qmax, with u = f 2^-24, as a float. The sum is never negative, so truncation
+// is the floor. One rounding of the product for words 2 j, one of the product and
+// sum together for words 2 j + 1: written out, so that the compiler's choice of
+// contraction cannot tell its instances apart (the popcount and the batched scan of
+// one search must see the same quantised query). A pair that is not live has scale
+// 0, so it quantises to 0, as does a NaN (the median with a NaN is the smaller of
+// the other two).
 __device__ __forceinline__ float round_even_word(float v, float rmin, float scale, uint32_t f, float qmax) {
 #pragma clang fp contract(off)
   const float x = (v - rmin) * scale;

@@ -75,6 +75,42 @@ def test_quantized_query_matches_oracle_at_bq(bq):
     print(f"B_q={bq}: {flips} quantised coordinates differ from FP64")
 
 
+@pytest.mark.parametrize("words", [8, 9, 11, 12, 13, 15, 16, 17])
+def test_wide_quantisation_at_bq8(words):
+    """8-bit rounding at the widths with a register bound of their own and beside
+    them, against its definition, floor((r - min) / step + u): equal wherever that
+    argument is at least 2e-3 from an integer (residuals good to 1e-6 of their range
+    give 3e-4 of the 255 levels), one level off at most elsewhere."""
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    _say(f"wide quantisation {words}")
+    dim, dp, nlist, nq, nprobe, seed = 64 * words - 9, 64 * words, 12, 40, 5, 4300
+    rng = np.random.default_rng(words)
+    P = np.linalg.qr(rng.standard_normal((dp, dp)))[0]
+    cent = rng.standard_normal((nlist, dim)).astype(np.float32)
+    data = rng.standard_normal((100, dim)).astype(np.float32)
+    idx = R.Index(dim, nlist, seed=seed, bq=8)
+    idx.build_rotation(data, cent, (np.arange(100) % nlist).astype(np.int32), P)
+    crot = (cent.astype(np.float64) @ P[:dim]).astype(np.float32)
+    q = rng.standard_normal((nq, dim)).astype(np.float32)
+    lists = np.stack([rng.permutation(nlist)[:nprobe] for _ in range(nq)]).astype(np.int32)
+    qc = torch.from_numpy(q).cuda()
+    qu, scal = R.rbq_debug_quantize(idx.h, qc, torch.from_numpy(lists).cuda(), dp, qid_base=9)
+    qu, scal = qu.cpu().numpy().reshape(nq, nprobe, dp), scal.cpu().numpy().reshape(nq, nprobe, 4)
+    rot = R.rbq_debug_rotate(idx.h, qc, dp).cpu().numpy()
+    for qi in range(nq):
+        for r in range(nprobe):
+            lid = int(lists[qi, r])
+            res = (rot[qi] - crot[lid]).astype(np.float64)
+            v = (res - res.min()) * 255 / (res.max() - res.min()) + O.rounding_uniforms_fast(seed, 9 + qi, lid, dp)
+            want = np.clip(np.floor(v), 0, 255)
+            clear = np.abs(v - np.rint(v)) > 2e-3
+            assert (qu[qi, r][clear] == want[clear]).all() and clear.mean() > 0.98, (qi, r)
+            assert (np.abs(qu[qi, r] - want) <= 1).all()
+            assert scal[qi, r, 3] == qu[qi, r].sum(dtype=np.int64)
+    idx.close()
+
+
 def test_fp4_scan_limited_to_bq4():
     import torch
     from paper_2405_12497_amd import rabitq as R
