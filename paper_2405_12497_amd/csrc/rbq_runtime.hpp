@@ -178,6 +178,10 @@ struct rbq_index {
   // autotuned choices per batch-size bucket (empty: defaults)
   std::vector<rbq::TuneEntry> tune;
   rbq::TuneEntry tuned_for(int64_t nq) const;
+  // fewest (query, list) pairs whose batched scan the automatic choice could not
+  // allocate: from there on it stays with the popcount scan instead of failing,
+  // freeing buffers (which drops captured graphs) and searching again on each call
+  int64_t auto_popcnt_pairs = INT64_MAX;
 
   ~rbq_index();
   std::vector<rbq::DBuf*> all_buffers();

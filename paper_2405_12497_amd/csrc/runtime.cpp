@@ -499,6 +499,7 @@ rbq_status build_impl(rbq_index* idx, const float* data, int64_t n, const std::v
   idx->built = false;
   for (DBuf* b : idx->all_buffers()) b->release();
   idx->graphs_clear();
+  idx->auto_popcnt_pairs = INT64_MAX;
   idx->mlp.has_model = false;   // a model's features refer to the old lists
   idx->h_P.swap(P);
   idx->h_cent = cent;
@@ -1232,7 +1233,10 @@ rbq_status rbq::search_locked(rbq_index* idx, const float* queries, int64_t nq, 
   const bool learned = !o.nprobe_per_query && o.use_learned_nprobe && idx->mlp.has_model;
   // a per-query nprobe is about half its largest value on average
   const bool choose = kernel == RBQ_SCAN_AUTO;
-  if (choose) kernel = auto_scan_kernel(idx, nq, o.nprobe * (learned || o.nprobe_per_query ? 0.5 : 1.0));
+  if (choose)
+    kernel = nq * o.nprobe < idx->auto_popcnt_pairs
+                 ? auto_scan_kernel(idx, nq, o.nprobe * (learned || o.nprobe_per_query ? 0.5 : 1.0))
+                 : RBQ_SCAN_POPCNT;
   // A query's candidate segment reserves a slot for each probed code, so a
   // batch is searched in sub-batches whose segments stay within kSegBudget
   // (same stream and workspace; queries keep their ids qid_base + i).
@@ -1302,6 +1306,7 @@ rbq_status rbq::search_locked(rbq_index* idx, const float* queries, int64_t nq, 
                                        exact ? budget : 0, &m);
     if (rs == RBQ_ENOMEM && choose && kernel == RBQ_SCAN_MFMA) {   // it takes a byte per pair and dimension more
       kernel = RBQ_SCAN_POPCNT;
+      idx->auto_popcnt_pairs = std::min(idx->auto_popcnt_pairs, nq * o.nprobe);
       for (DBuf* b : {&idx->ws.qu8, &idx->ws.mf_pairs, &idx->ws.mf_rows, &idx->ws.mf_units}) b->release();
       m = std::min(rows, nq - q0);
       rs = graph ? rbq::search_graph(idx, qs, m, os, kernel, chunk, mf_rg, learned, oi, od, st, &npq, &stride)

@@ -147,6 +147,36 @@ def test_allocation_failure_reports_enomem_and_recovers():
     assert (ids.cpu().numpy() == want).mean() > 0.95
 
 
+def test_automatic_scan_without_memory_for_its_buffers():
+    """The automatic choice falls back to the popcount scan where the batched scan's
+    buffers cannot be allocated, and later searches of that size allocate nothing."""
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    _say("automatic scan, allocation failure")
+    rng = np.random.default_rng(16)
+    nlist, dim, nq = 300, 700, 700   # past the automatic choice's line
+    cent = rng.standard_normal((nlist, dim)).astype(np.float32)
+    assign = np.repeat(np.arange(nlist), 150).astype(np.int32)
+    data = (cent[assign] + rng.standard_normal((len(assign), dim))).astype(np.float32)
+    q = torch.from_numpy((cent[rng.integers(0, nlist, nq)] + rng.standard_normal((nq, dim))).astype(np.float32)).to(_dev())
+    other = _index(data[:300], cent[:1], np.zeros(300, np.int32))
+    for graph in (False, True):
+        idx = _index(data, cent, assign)
+        want = idx.search(q, 10, 24, scan_kernel=R.RBQ_SCAN_POPCNT, use_graph=graph)   # the popcount scan's buffers
+        for _ in range(3):
+            R.rbq_debug_fail_alloc_after(1)   # the first time, of a buffer that only the batched scan needs
+            got = idx.search(q, 10, 24, use_graph=graph)
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        try:   # the last search left the injected failure to the next allocation
+            with pytest.raises(R.RbqError) as e:
+                other.build(data[:300], cent[:1], np.zeros(300, np.int32))
+            assert e.value.status == R.RBQ_ENOMEM
+        finally:
+            R.rbq_debug_fail_alloc_after(0)
+        idx.close()
+    other.close()
+
+
 def test_save_load_roundtrip(tmp_path):
     import torch
     from paper_2405_12497_amd import rabitq as R
