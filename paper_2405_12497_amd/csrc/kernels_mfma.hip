@@ -110,7 +110,7 @@ __device__ void mfma_unit(const SearchDev& s, int64_t start, int64_t end, const 
     int pcp = 0;
     if constexpr (F4) {
       // lane group grp: dimensions 128 t2 + 32 grp .. +31, half (grp & 1) of
-      // word 2 t2 + (grp >> 1); every word read is issued before the first product
+      // word 2 t2 + (grp >> 1); four words' reads are issued before their products
       const uint32_t keep32 = pvalid ? 0xFFFFFFFFu : 0u;
       const uint32_t* c32 = reinterpret_cast<const uint32_t*>(s.codes);
       f32x4 accf[RG];
@@ -133,23 +133,14 @@ __device__ void mfma_unit(const SearchDev& s, int64_t start, int64_t end, const 
         const uint32_t v = c32[2 * code_word_index(p, min(w, W - 1), W) + (grp & 1)];
         return w < W ? v & keep32 : 0u;
       };
-      if constexpr (WS > 0) {
-        constexpr int T2 = (WS + 1) / 2;
-        uint32_t bw[T2];
+      const int T2 = (W + 1) / 2;
+      for (int t0 = 0; t0 < T2; t0 += 4) {
+        uint32_t bw[4];
 #pragma unroll
-        for (int t2 = 0; t2 < T2; ++t2) bw[t2] = load(t2);
+        for (int j = 0; j < 4; ++j) bw[j] = load(min(t0 + j, T2 - 1));
 #pragma unroll
-        for (int t2 = 0; t2 < T2; ++t2) step(bw[t2], t2);
-      } else {
-        const int T2 = (W + 1) / 2;
-        for (int t0 = 0; t0 < T2; t0 += 4) {
-          uint32_t bw[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) bw[j] = load(min(t0 + j, T2 - 1));
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (t0 + j < T2) step(bw[j], t0 + j);
-        }
+        for (int j = 0; j < 4; ++j)
+          if (t0 + j < T2) step(bw[j], t0 + j);
       }
 #pragma unroll
       for (int h = 0; h < RG; ++h) {
@@ -687,8 +678,6 @@ void allow_lds(const void* f, size_t bytes) {
 }
 
 }  // namespace
-
-bool mfma_available() { return true; }
 
 int mfma_row_groups(int dp, bool f4, int npl, int want) {
   if (scan_frag_available(dp / 64, npl)) return 2;

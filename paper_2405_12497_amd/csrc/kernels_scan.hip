@@ -38,10 +38,11 @@ constexpr int kWaves = kThreads / kWave;
 // rotated-space form of P^T (q_r - c)), b = ||r|| (= ||q_r - c|| since P is
 // orthogonal), v_l / v_r = min / max of r / b, Delta = (v_r - v_l) / (2^B_q - 1)
 // and the randomized rounding q_u[i] = min(2^B_q - 1, floor((r_i/b - v_l)/Delta + u_i)),
-// written as s.npl bit planes (and for the batched scan as int8 q_u - s.qoff, or in the fragment scan's order and format), plus the pair's
-// estimator constants. prep_pair does this for pair g = (query q, list) from
-// the residual rv (this lane's coordinates t * 64 + lane, WS >= W words, a
-// compile-time bound) and the query's norm qn.
+// written as s.npl bit planes (and for the batched scan as int8 q_u - s.qoff, or in
+// the fragment scan's order and format), plus the pair's estimator constants.
+// prep_pair does this for pair g = (query q, list) from the residual rv (this lane's
+// coordinates t * 64 + lane, WS >= W words, a compile-time bound) and the query's
+// norm qn, for the codes and B_q that the fragment scan does not take.
 template <int WS, int NPL>
 __device__ __forceinline__ void prep_pair(const SearchDev& s, int64_t g, int64_t q, int list, const float* rv,
                                           float qn) {
@@ -68,8 +69,6 @@ __device__ __forceinline__ void prep_pair(const SearchDev& s, int64_t g, int64_t
   const int npl = NPL > 0 ? NPL : s.npl;   // bit planes (B_q), compile-time when given
   uint64_t* pl = s.planes + g * npl * W;
   int8_t* q8 = s.qu8 ? s.qu8 + g * s.dp : nullptr;
-  const uint32_t q8_at = (uint32_t)(s.frag ? frag_pos(lane) : lane);
-  const float q8_scale = frag_scale(lane);
   // with the MFMA scan, only the pairs whose first chunk is a bootstrap chunk
   // (scanned by the popcount phase 0) need bit planes
   const int64_t r = g - q * s.nprobe;
@@ -90,7 +89,7 @@ __device__ __forceinline__ void prep_pair(const SearchDev& s, int64_t g, int64_t
       const float x = (rv[t] - rmin) * scale;
       const int qu = min(s.qmax, (int)floorf(x + u));
       sq += qu;
-      if (q8) q8[(uint32_t)(t * kWave) + q8_at] = s.frag ? frag_byte(qu, q8_scale) : (int8_t)(qu - s.qoff);
+      if (q8) q8[(uint32_t)i] = (int8_t)(qu - s.qoff);
       if (!planes) continue;
       if constexpr (NPL > 0) {   // all ballots first, then one branch for the stores
         uint64_t w[NPL > 0 ? NPL : 1];
@@ -1518,9 +1517,9 @@ hipError_t launch_prep(const SearchDev& s, bool units, hipStream_t st) {
     return hipGetLastError();
   }
   // the rest: one pair per wave, two up to W = 8. Codes of up to 16 words come here
-  // with B_q > 4 only; 4000 queries x 40 lists at B_q = 8 take 192 us with the exact
-  // width at W = 12 and 208 us with the 16-word bound; at W = 15 it makes no
-  // difference (230 us).
+  // with B_q > 4 only; 4000 queries x 40 lists at B_q = 8 take 186 us with the exact
+  // width at W = 12 and 201 us with the 16-word bound; at W = 15 it makes no
+  // difference (225 us).
   const bool p4 = s.npl == 4;
 #define RBQ_PREP(WS_, PPW_, NPL_) \
   hipLaunchKernelGGL((k_prep_reg<WS_, PPW_, NPL_>), grid(PPW_), dim3(kThreads), 0, st, s)
@@ -1691,10 +1690,6 @@ hipError_t launch_finalize_split(const SearchDev& s, int W, uint64_t* part, int3
     hipLaunchKernelGGL(k_fin_merge, dim3((unsigned)((s.nq + kWaves - 1) / kWaves)), dim3(kThreads), 0, st, s, W,
                        part, pst);
   return hipGetLastError();
-}
-
-hipError_t launch_finalize(const SearchDev& s, hipStream_t st) {
-  return launch_finalize_split(s, 1, nullptr, nullptr, st);
 }
 
 hipError_t launch_debug_pack(const uint8_t* qu, int dp, int W, int npl, int qoff, int frag, float b, float vl, float delta,

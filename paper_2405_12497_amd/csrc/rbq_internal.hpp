@@ -411,10 +411,9 @@ hipError_t launch_scan_popcnt(const SearchDev& s, int phase, int grid, hipStream
 hipError_t launch_group_mfma(const SearchDev& s, hipStream_t st);
 hipError_t launch_scan_mfma(const SearchDev& s, int phase, int grid, hipStream_t st);
 hipError_t launch_tau(const SearchDev& s, hipStream_t st);
-hipError_t launch_finalize(const SearchDev& s, hipStream_t st);
 // Query order for the rerank: queries by descending per-query nprobe (64
 // bins; order within a bin unspecified), so the longest reranks start first.
-// hist: 128 int32 of scratch; order: nq int32.
+// order: nq int32.
 hipError_t launch_query_order(const int32_t* nprobe_q, int64_t nq, int nprobe, int32_t* order, hipStream_t st);
 
 // debug: list scan with a given quantised query

@@ -129,8 +129,6 @@ struct MlpState {
   DBuf w32, wbf, wfrag, grad, m, v, act;   // wfrag: BF16 weights in MFMA fragment order
 };
 
-// MFMA scan availability (kernels_mfma.hip).
-bool mfma_available();
 // Zero-fill by a kernel (no memset node when a caller captures the stream).
 hipError_t launch_zero_u32(void* p, int64_t nwords, hipStream_t st);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);

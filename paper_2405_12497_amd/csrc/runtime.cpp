@@ -1355,16 +1355,12 @@ rbq_status rbq::search_in_arena(rbq_index* idx, const float* queries, int64_t nq
   std::lock_guard<std::mutex> lock(idx->mu);
   if (idx->prof.on) return fail(RBQ_ESTATE, "profiling is enabled (its events would be allocated)");
   if (idx->done_event) HIPCHK(hipStreamWaitEvent(st, idx->done_event, 0));
-  const TuneEntry tc = idx->tuned_for(nq);   // as rbq_search chooses them
+  const TuneEntry tc = idx->tuned_for(nq);   // tuned choices, as rbq_search
   int kernel = o.scan_kernel == RBQ_SCAN_AUTO ? tc.kernel : o.scan_kernel;
   const int chunk = std::min(tc.chunk, kMaxP0 + 1 - o.k);
   const int mf_rg = tc.mf_rg;
   if (o.rerank_waves == 0) o.rerank_waves = tc.fin_w;
-  if (kernel == RBQ_SCAN_AUTO || (kernel == RBQ_SCAN_MFMA && !rbq::mfma_available())) {
-    if (kernel == RBQ_SCAN_MFMA && o.scan_kernel == RBQ_SCAN_MFMA)
-      return fail(RBQ_EUNSUPPORTED, "the MFMA scan kernel is not available in this library");
-    kernel = RBQ_SCAN_POPCNT;
-  }
+  if (kernel == RBQ_SCAN_AUTO) kernel = RBQ_SCAN_POPCNT;   // the least scratch
   const bool learned = !o.nprobe_per_query && o.use_learned_nprobe && idx->mlp.has_model;
   o.rerank_waves = fin_waves(o.rerank_waves, graph_rows(nq), o.k);
   // the index's own workspace is set aside; every buffer the search ensures is carved
@@ -1687,7 +1683,6 @@ extern "C" rbq_status rbq_debug_scan(rbq_index* idx, int32_t list, const uint8_t
   if (list < 0 || list >= idx->nlist) return fail(RBQ_EINVAL, "list out of range");
   if (kernel != RBQ_SCAN_POPCNT && kernel != RBQ_SCAN_MFMA && kernel != RBQ_SCAN_MFMA_FP4)
     return fail(RBQ_EINVAL, "kernel must be POPCNT, MFMA or MFMA_FP4");
-  if (kernel == RBQ_SCAN_MFMA && !rbq::mfma_available()) return fail(RBQ_EUNSUPPORTED, "MFMA scan not available");
   if (kernel == RBQ_SCAN_MFMA_FP4 && idx->prm.bq > 4)
     return fail(RBQ_EUNSUPPORTED, "the FP8 x FP4 scan holds query values up to 15 exactly (B_q <= 4)");
   for (const void* p : {(const void*)qu, (const void*)ip, (const void*)pc, (const void*)est,
@@ -1864,10 +1859,10 @@ extern "C" rbq_status rbq_autotune(rbq_index* idx, const float* queries, int64_t
   std::vector<TuneEntry> table;
   const int chunks[] = {256, 512, 1024, 2048};
   std::vector<int> kernels = {RBQ_SCAN_POPCNT};
-  if (rbq::mfma_available()) kernels.push_back(RBQ_SCAN_MFMA);
+  kernels.push_back(RBQ_SCAN_MFMA);
   // where the fragment scan serves both, one of them is enough
   const int npl = idx->prm.bq <= 4 ? 4 : 8;
-  if (rbq::mfma_available() && idx->prm.bq <= 4 && !scan_frag_available(idx->W, npl)) kernels.push_back(RBQ_SCAN_MFMA_FP4);
+  if (idx->prm.bq <= 4 && !scan_frag_available(idx->W, npl)) kernels.push_back(RBQ_SCAN_MFMA_FP4);
   for (int64_t m : sizes) {
     TuneEntry best;
     float best_ms = 1e30f;
