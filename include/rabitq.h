@@ -11,7 +11,7 @@
  *   - the query phase (Algorithm 2; Sec. 3.2-3.3) and IVF search with the
  *     error-bound rerank (Sec. 4): rotate, probe the nearest lists, quantise
  *     the query to B_q bits (1..8, default 4) with randomised rounding per (query, list),
- *     integer <x_b, q_u> by AND + popcount or int8 MFMA, the unbiased estimate,
+ *     integer <x_b, q_u> by AND + popcount or MFMA, the unbiased estimate,
  *     the lower distance bound, exact rerank, top-k.
  *
  * Conventions for every function:
@@ -180,9 +180,12 @@ rbq_status rbq_index_create(const rbq_params* p, rbq_index** out);
  * Each pointer may be host or device memory independently; device data is
  * reordered into list order on the device, host data is staged in blocks.
  * n is below 2^31 - 64, and 64*ceil(n/64) * code_bits/64 below 2^32 (32-bit
- * word offsets in the scan). Errors: RBQ_EINVAL for a NULL or out-of-range
- * argument (assign outside [0, nlist), non-finite values, a rank-deficient
- * draw), RBQ_ENOMEM / RBQ_EDEVICE from the device. Synchronises `stream`.
+ * word offsets in the scan). Rows of data are not checked: one that holds a NaN
+ * or an infinity, or whose norm overflows, is stored and with RBQ_METRIC_L2
+ * disturbs no other row's ranking (the inner-product metrics need finite rows).
+ * Errors: RBQ_EINVAL for a NULL or out-of-range argument (assign outside
+ * [0, nlist), non-finite centroids or draw, a rank-deficient draw), RBQ_ENOMEM /
+ * RBQ_EDEVICE from the device. Synchronises `stream`.
  * Rebuilding an index replaces its contents (and drops a learned-nprobe
  * model, whose features refer to the old lists). */
 rbq_status rbq_index_build(rbq_index* idx, const float* data, int64_t n,
@@ -214,7 +217,7 @@ rbq_status rbq_index_build_rotation(rbq_index* idx, const float* data, int64_t n
  * rows (empty lists keep theirs). The means are summed in 64-bit fixed point,
  * so the result does not depend on the order of the parallel additions: the
  * same inputs and seed give the same bits. Temporary device memory: the data
- * (if given on the host), the sample, and up to 1 GiB of distances.
+ * (if given on the host), the sample, and up to 64 MiB of nearest lists per row.
  * Errors: RBQ_EINVAL (NULL, n, dim or nlist out of range, nlist above the
  * sample size, non-finite data), RBQ_ENOMEM / RBQ_EDEVICE. Synchronises. */
 rbq_status rbq_kmeans(const float* data, int64_t n, int32_t dim, int32_t nlist, int32_t iters,
@@ -247,11 +250,12 @@ rbq_status rbq_index_set_eps0(rbq_index* idx, float eps0);
 /* rbq_search for callers that cannot allocate device memory (code under HIP
  * stream/graph capture, serving loops with a fixed memory budget, harnesses
  * that forbid hipMalloc): the same kernels and results as rbq_search on the
- * same arguments, with every workspace buffer carved from a device array of
- * RBQ_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs on
- * (from the first call on that GPU until the process ends). Nothing is
- * allocated or freed, and no HIP memset is issued (every buffer the search
- * needs zeroed is cleared by its own kernels).
+ * same arguments (RBQ_SCAN_AUTO without a tuned choice runs the popcount scan,
+ * whose workspace is smaller; results are identical), with every workspace buffer
+ * carved from a device array of RBQ_NOALLOC_SCRATCH_BYTES that the library holds
+ * on each GPU it runs on (from the first call on that GPU until the process ends).
+ * Nothing is allocated or freed, and no HIP memset is issued (every buffer the
+ * search needs zeroed is cleared by its own kernels).
  *   queries, out_ids, out_dists, opts->nprobe_per_query: device pointers
  *   (layouts as rbq_search); opts->use_graph must be 0; no statistics.
  * Errors: RBQ_EINVAL for a search whose workspace exceeds the array (the
@@ -285,10 +289,10 @@ const char* rbq_last_error(void);
  * sample itself), it times whole searches of the first rows of `queries` (host
  * or device, nq x dim, nq <= 2^24) at (k, nprobe): every chunk length (codes
  * per work unit of the persistent scans: 256, 512, 1024, 2048) with every scan
- * kernel (popcount, int8 MFMA, and FP8 x FP4 MFMA when B_q <= 4), then, for a
- * batched (MFMA) scan, 16, 32 or 64
- * query rows per work unit, then, for batches that split a query's rerank over
- * several waves, rerank waves 1..64 at the best choice. A search with
+ * kernel (popcount, MFMA, and for B_q <= 4 and codes above 1024 bits FP8 x FP4
+ * MFMA), then, for an int8 or FP8 x FP4 scan, 16, 32 or 64 query rows per work
+ * unit, then, for batches that split a query's rerank over several waves, rerank
+ * waves 1..64 at the best choice. A search with
  * scan_kernel = RBQ_SCAN_AUTO and rerank_waves = 0 then uses the choices of
  * the bucket its batch size falls in (up to the geometric middle between two
  * tuned sizes); the chunk length applies to every later search. Results stay
@@ -303,8 +307,9 @@ typedef struct {
   int32_t scan_kernel;   /* RBQ_SCAN_POPCNT, RBQ_SCAN_MFMA or RBQ_SCAN_MFMA_FP4 */
   int32_t rerank_waves;  /* 0: chosen from the batch size */
   float ms;              /* the trial search's time at the bucket's size */
-  int32_t mfma_row_groups; /* batched scans: groups of 16 queries that share each
-                              expanded code fragment (1, 2, 4; 0: one) */
+  int32_t mfma_row_groups; /* int8 and FP8 x FP4 scans: groups of 16 queries that share
+                              each expanded code fragment (1, 2, 4; 0: one); the FP6 x
+                              FP4 scan always takes 32 queries */
 } rbq_tune_entry;
 
 /* The autotuner's table: up to max_entries entries (host) and *count, the

@@ -21,7 +21,7 @@
 // Per 32 x 32 block at W = 12 that is 276 vector instructions where four
 // 16 x 16 int8 blocks took about 680.
 // Bound by their issue and by the candidates' stores: 10,000 queries x 128 lists of
-// 2 M codes at D = 768 take 1170 us (2343 on 16 x 16 int8 blocks), 256 x 8 lists at
+// 2 M codes at D = 768 take 1115 us (2343 on 16 x 16 int8 blocks), 256 x 8 lists at
 // D = 960 72 us (90).
 #include "rbq_internal.hpp"
 #include "rbq_runtime.hpp"

@@ -1,6 +1,8 @@
-// Batched scan: the integer <x_b, q_u> of Sec. 3.3.2 for all (query, code)
-// pairs of one IVF list at once, as an int8 matrix product on the MFMA units:
-//   IP[pairs x codes] = Qu[pairs x D] (values 0..15) * Xb[D x codes] (0/1).
+// Batched scan in block form, for B_q > 4 and for codes above 16 words
+// (kernels_frag.hip takes the rest), and the grouping of pairs by list for both:
+// the integer <x_b, q_u> of Sec. 3.3.2 for all (query, code) pairs of one IVF list
+// at once, as an int8 matrix product on the MFMA units:
+//   IP[pairs x codes] = Qu[pairs x D] (B_q bits, less 128 for 8) * Xb[D x codes] (0/1).
 // The paper evaluates the same batched contraction with 4-bit look-up tables
 // in SIMD registers; on CDNA4 the contraction maps onto v_mfma_i32_16x16x64_i8.
 //

@@ -267,7 +267,7 @@ hipError_t launch_centroid_dist(const float* Q, int64_t nq, int dim, const float
                                 const float* cn, int nlist, float* D, float* gmin, hipStream_t st,
                                 const uint16_t* Chi = nullptr, const uint16_t* Clo = nullptr);
 // The FP32 query rotation qrot = Q * P (P is [dim x dp]) and launch_centroid_dist's
-// outputs, in one launch when the distances use 128-wide tiles.
+// outputs, in one launch above 8 queries.
 hipError_t launch_rotate_centroid(const float* Q, int64_t nq, int dim, const float* P, int dp, float* qrot,
                                   const float* Ct, const float* cn, int nlist, float* D, float* gmin,
                                   hipStream_t st);
