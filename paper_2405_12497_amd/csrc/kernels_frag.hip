@@ -18,7 +18,7 @@
 //     the queries' fragments take 6 W registers instead of 8 W;
 //   - a lane owns one query (the output's column), so the query's constants
 //     sit in registers; the 32 codes' factors come from LDS by broadcast reads;
-// Per 32 x 32 block at W = 12 that is 276 vector instructions where four
+// Per 32 x 32 block at W = 12 that is 290 vector instructions where four
 // 16 x 16 int8 blocks took about 680.
 // Bound by their issue and by the candidates' stores: 10,000 queries x 128 lists of
 // 2 M codes at D = 768 take 1115 us (2343 on 16 x 16 int8 blocks), 256 x 8 lists at
