@@ -74,3 +74,42 @@ def test_fp32_rotation_and_centroid_distances(dim, nlist):
     want = np.sort(((q[:, None].astype(np.float64) - data[None]) ** 2).sum(-1), 1)[:, :5]
     assert (np.abs(got.cpu().numpy() - want) <= want * tol + 1e-12).all()
     idx.close()
+
+
+@pytest.mark.parametrize("dim,rot", [(64, 0), (100, 0), (100, 1), (768, 0), (768, 1)])
+def test_buffers_at_any_float_address(dim, rot):
+    """Queries, data and k-means input that begin 4, 8 or 12 bytes past a multiple of
+    16, which the kernels read four floats at a time: the results are those of the
+    same values at an aligned address."""
+    import torch
+    from paper_2405_12497_amd import rabitq as R
+    print(f"[address {dim} {rot}]", flush=True)
+    rng = np.random.default_rng(dim + rot)
+    n, nlist, nq = 1300, 24, 700
+    data = rng.standard_normal((n, dim)).astype(np.float32)
+    q = rng.standard_normal((nq, dim)).astype(np.float32)
+
+    def at(x, shift):
+        buf = torch.zeros(x.size + 8, device="cuda")
+        v = buf[shift:shift + x.size].view(x.shape)
+        v.copy_(torch.from_numpy(x))
+        assert v.data_ptr() % 16 == 4 * shift % 16
+        return v
+
+    ref = None
+    for shift in (0, 1, 2, 3):
+        d = at(data, shift)
+        cent, assign = R.rbq_kmeans(d, nlist, iters=2, seed=5)
+        idx = R.Index(dim, nlist, rot_precision=R.RBQ_ROT_BF16X3 if rot else R.RBQ_ROT_FP32, seed=9)
+        idx.build(d, cent, assign)
+        out = [cent, assign]
+        for m in (1, 5, 40, nq):
+            for scan in (R.RBQ_SCAN_POPCNT, R.RBQ_SCAN_MFMA):
+                ids, dist, _ = idx.search(at(q[:m], shift), 10, 8, scan_kernel=scan)
+                out += [ids, dist]
+        torch.cuda.synchronize()
+        out = [torch.as_tensor(x).cpu() for x in out]
+        ref = ref or out
+        for a, b in zip(ref, out):
+            assert torch.equal(a, b), shift
+        idx.close()
